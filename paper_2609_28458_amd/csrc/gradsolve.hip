@@ -305,16 +305,16 @@ void solve_shape(const gs_solve_args* a, int* grid, int* block, int64_t* limit =
   if (limit) *limit = lim;
 }
 
-// Split of a forward launch with `wide` trajectories on 16-lane groups.  The
-// group workgroups (block / 16 groups each) and the single-lane workgroups
+// Split of a launch with `wide` trajectories on groups of `lanes_each` lanes.
+// The group workgroups (block / lanes_each groups each) and the single-lane workgroups
 // draw from separate persistent queues.  Both together stay within `limit`
 // (a persistent grid must be resident as a whole), except that each side
 // that has trajectories gets at least one workgroup: the single lanes keep
 // the workgroups they need, up to half of the limit, and the groups take
 // the rest, as many as start every wide trajectory at once if that fits.
-void wide_split(int64_t n, int64_t n_wide, int block, int64_t limit, int* wide_blocks,
-                int* grid) {
-  const int64_t per_block = block / gs::kGroup;
+void wide_split(int64_t n, int64_t n_wide, int block, int lanes_each, int64_t limit,
+                int* wide_blocks, int* grid) {
+  const int64_t per_block = block / lanes_each;
   const int64_t want_w = (n_wide + per_block - 1) / per_block;
   const int64_t need_s = (n - n_wide + block - 1) / block;
   const int64_t keep_s = std::min<int64_t>(need_s, std::max<int64_t>(limit / 2, 1));
@@ -340,7 +340,7 @@ gs_status launch_solve_all(const gs_solve_args* a, bool defer = true) {
     gs_host::launch_stiff(a->rhs, P, grid, block, s);
     return hipGetLastError() == hipSuccess ? GS_OK : GS_ERR_HIP;
   }
-  if (P.n_wide > 0) wide_split(P.n, P.n_wide, block, limit, &P2.wide_blocks, &grid);
+  if (P.n_wide > 0) wide_split(P.n, P.n_wide, block, gs::kGroup, limit, &P2.wide_blocks, &grid);
   ops(a->rhs, a->tableau).solve(P2, grid, block, s);
   if (P.pending) ops(a->rhs, a->tableau).short_steps(P, s);
   return hipGetLastError() == hipSuccess ? GS_OK : GS_ERR_HIP;
@@ -548,7 +548,7 @@ gs_status gs_solve_vjp(const gs_solve_args* fwd, const gs_vjp_args* v) {
     if (per_cu > 0) grid = (int)std::min<int64_t>(grid, (int64_t)per_cu * num_cus());
   }
   if (grid < 1) return GS_ERR_INVALID;
-  if (P.n_wide > 0) wide_split(P.n, P.n_wide, block, grid, &P.wide_blocks, &grid);
+  if (P.n_wide > 0) wide_split(P.n, P.n_wide, block, gs::kGroup, grid, &P.wide_blocks, &grid);
   V.R_total = v->R;
   V.ybar_out = v->ybar_out;
   V.ybar_final = v->ybar_final;
@@ -573,6 +573,29 @@ gs_status gs_solve_vjp(const gs_solve_args* fwd, const gs_vjp_args* v) {
 }
 
 namespace {
+// Tangent lanes of a sensitivity solve with M columns: the group, and the
+// lanes one trajectory takes with every group of G - 1 columns on its own.
+int tangent_group(int M) { return M == 1 ? 2 : 4; }
+int64_t tangent_lanes_each(int M) {
+  const int G = tangent_group(M);
+  return (int64_t)G * ((M + G - 2) / (G - 1));
+}
+// All columns on tangent lanes in one launch, or two columns per launch as
+// dual numbers in one lane.  Tangent lanes evaluate the value's right-hand
+// side once per lane, so they cost about twice the arithmetic, but the
+// columns of a small ensemble then fill SIMDs that would stand idle and the
+// launches do not follow one another.  The line lies where the lanes are one
+// and a half wavefronts per SIMD for each launch they replace (Tsit5 orbits, 2
+// columns: 16,000 orbits 445 against 709 us, 32,000 orbits 737 against 700;
+// 9 columns: 32,000 orbits 1.85 against 3.29 ms, 64,000 orbits 3.25 against
+// 3.22; 1 column: 32,000 orbits 441 against 522 us, 64,000 744 against 509).
+// Pairs without dual-number kernels always take tangent lanes.
+bool on_tangent_lanes(const gs_solve_args* a, int M, const Ops& o) {
+  if (!o.sens_dual[a->K > 0 ? 1 : 0]) return true;
+  const int64_t launches = (M + 1) / 2;
+  return a->n * tangent_lanes_each(M) <= launches * 6 * 64 * (int64_t)num_cus();
+}
+
 // The launches of a sensitivity solve whose arguments have been checked.
 void sens_launches(const gs_solve_args* a, const gs_sens_args* sa) {
   hipStream_t s = static_cast<hipStream_t>(a->stream);
@@ -586,28 +609,46 @@ void sens_launches(const gs_solve_args* a, const gs_sens_args* sa) {
   if (a->order)
     hipLaunchKernelGGL(fill_status_kernel, dim3(fill_grid(P.n)), dim3(256), 0, s, P.status, P.n,
                        (int32_t)GS_TRAJ_NOT_RUN);
+  const gs_host::Ops& o = ops(a->rhs, a->tableau);
+  // The grid's limit: the caller's, or the occupancy of the variant.
+  auto limit_of = [&](auto&& query) {
+    if (a->grid > 0) return (int64_t)a->grid;
+    int per_cu = 0;
+    S.occupancy_out = &per_cu;
+    query();
+    S.occupancy_out = nullptr;
+    return (int64_t)std::max(per_cu, 1) * num_cus();
+  };
+  if (on_tangent_lanes(a, sa->M, o)) {
+    const int G = tangent_group(sa->M);
+    Params P2 = P;
+    P2.n_wide = 0;
+    S.m0 = 0;
+    S.m = sa->M;
+    for (int m = 0; m < sa->M; ++m) S.col[m] = sa->cols[m];
+    const int64_t need = (a->n * tangent_lanes_each(sa->M) + block - 1) / block;
+    const int64_t limit = limit_of([&] { o.sens_lanes(P2, S, G, 0, block, s); });
+    hipLaunchKernelGGL(reset_queues_kernel, dim3(1), dim3(64), 0, s, P.counters, 0ll);
+    o.sens_lanes(P2, S, G, (int)std::min<int64_t>(limit, need), block, s);
+    return;
+  }
   // Two columns per launch; each launch integrates the solution again and
   // rewrites the same values.
   for (int m0 = 0; m0 < sa->M; m0 += 2) {
     const int mm = std::min(2, sa->M - m0);
     S.m0 = m0;
-    for (int m = 0; m < 4; ++m) S.col[m] = m < mm ? sa->cols[m0 + m] : -1;
+    S.m = mm;
+    for (int m = 0; m < 2; ++m) S.col[m] = m < mm ? sa->cols[m0 + m] : -1;
     const int64_t need = (a->n + block - 1) / block;
-    int64_t limit = a->grid;
-    if (a->grid <= 0) {
-      int per_cu = 0;
-      S.occupancy_out = &per_cu;
-      ops(a->rhs, a->tableau).sens(P, S, mm, 0, block, s);
-      S.occupancy_out = nullptr;
-      limit = (int64_t)std::max(per_cu, 1) * num_cus();
-    }
-    // The head of the order on 16-lane groups, as in a plain solve.
+    const int64_t limit = limit_of([&] { o.sens(P, S, mm, 0, block, s); });
+    // The head of the order on tangent lanes.
     Params P2 = P;
     int grid = (int)std::min<int64_t>(limit, need);
-    if (P.n_wide > 0) wide_split(P.n, P.n_wide, block, limit, &P2.wide_blocks, &grid);
+    if (P.n_wide > 0)
+      wide_split(P.n, P.n_wide, block, tangent_group(mm), limit, &P2.wide_blocks, &grid);
     hipLaunchKernelGGL(reset_queues_kernel, dim3(1), dim3(64), 0, s, P.counters,
                        (long long)P.n_wide);
-    ops(a->rhs, a->tableau).sens(P2, S, mm, grid, block, s);
+    o.sens(P2, S, mm, grid, block, s);
   }
 }
 

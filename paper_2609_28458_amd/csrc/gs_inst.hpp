@@ -93,15 +93,19 @@ template <class TB, class F, int M>
 void launch_sens_m(const gs::Params& P, const gs::SensParams& S, int grid, int block,
                    hipStream_t s) {
   if (P.K > 0) {
-    if (P.n_wide > 0)
-      launch_sens_v<TB, F, M, true, true>(P, S, grid, block, s);
-    else
-      launch_sens_v<TB, F, M, true, false>(P, S, grid, block, s);
+    if constexpr (gs::sens_fits_lane<TB, F>(true)) {
+      if (P.n_wide > 0)
+        launch_sens_v<TB, F, M, true, true>(P, S, grid, block, s);
+      else
+        launch_sens_v<TB, F, M, true, false>(P, S, grid, block, s);
+    }
   } else {
-    if (P.n_wide > 0)
-      launch_sens_v<TB, F, M, false, true>(P, S, grid, block, s);
-    else
-      launch_sens_v<TB, F, M, false, false>(P, S, grid, block, s);
+    if constexpr (gs::sens_fits_lane<TB, F>(false)) {
+      if (P.n_wide > 0)
+        launch_sens_v<TB, F, M, false, true>(P, S, grid, block, s);
+      else
+        launch_sens_v<TB, F, M, false, false>(P, S, grid, block, s);
+    }
   }
 }
 
@@ -112,6 +116,35 @@ void launch_sens(const gs::Params& P, const gs::SensParams& S, int M, int grid, 
     launch_sens_m<TB, F, 2>(P, S, grid, block, s);
   else
     launch_sens_m<TB, F, 1>(P, S, grid, block, s);
+}
+
+template <class TB, class F, int G, bool NODES>
+void launch_sens_lanes_v(const gs::Params& P, const gs::SensParams& S, int grid, int block,
+                         hipStream_t s) {
+  const void* fn = reinterpret_cast<const void*>(&gs::sens_lanes_kernel<TB, F, G, NODES>);
+  if (grid <= 0) {
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, block, 0) != hipSuccess) per_cu = 0;
+    *S.occupancy_out = per_cu;
+    return;
+  }
+  hipLaunchKernelGGL((gs::sens_lanes_kernel<TB, F, G, NODES>), dim3(grid), dim3(block), 0, s, P, S);
+}
+
+template <class TB, class F>
+void launch_sens_lanes(const gs::Params& P, const gs::SensParams& S, int G, int grid, int block,
+                       hipStream_t s) {
+  if (P.K > 0) {
+    if (G == 2)
+      launch_sens_lanes_v<TB, F, 2, true>(P, S, grid, block, s);
+    else
+      launch_sens_lanes_v<TB, F, 4, true>(P, S, grid, block, s);
+  } else {
+    if (G == 2)
+      launch_sens_lanes_v<TB, F, 2, false>(P, S, grid, block, s);
+    else
+      launch_sens_lanes_v<TB, F, 4, false>(P, S, grid, block, s);
+  }
 }
 
 template <class TB, class F>
@@ -132,6 +165,8 @@ Ops make_ops() {
                reinterpret_cast<const void*>(&gs::solve_kernel<TB, F, true, true>)}},
              inloop,
              &launch_solve<TB, F>, &launch_vjp<TB, F>, &launch_dense<TB, F>, &launch_sens<TB, F>,
+             &launch_sens_lanes<TB, F>,
+             {gs::sens_fits_lane<TB, F>(false), gs::sens_fits_lane<TB, F>(true)},
              &launch_short_steps<TB, F>,
              {gs::vjp_stages_in_lds<TB, F, false>() ? (TB::S - 1) * F::D * 8 : 0,
               gs::vjp_stages_in_lds<TB, F, true>() ? (TB::S - 1) * F::D * 8 : 0}};

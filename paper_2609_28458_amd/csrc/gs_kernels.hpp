@@ -364,30 +364,35 @@ __device__ double initial_step(const Inputs<F>& in, const double (&y)[F::D],
 // first stage is evaluated afresh) and keeps k[0], so several outputs in one
 // step each start from the same k[0].  A second stage array for it would
 // double the lane's largest live set.
+template <class TB, int D, class T>
+__device__ __forceinline__ void dense_poly(double h, double sigma, const T (&y_end)[D],
+                                           const T (&k)[TB::S][D], T (&out)[D]) {
+  constexpr int S = TB::S;
+  double w[S];
+  sfor<S>([&](auto J) {
+    constexpr int j = decltype(J)::value;
+    double acc = 0.0;
+    rfor<TB::DEG>([&](auto Q) {
+      constexpr int q = decltype(Q)::value;
+      acc = fma(acc, sigma, TB::Bs(j, q));
+    });
+    w[j] = TB::B(j) - acc * sigma;
+  });
+#pragma unroll
+  for (int c = 0; c < D; ++c) {
+    T acc = zero<T>();
+#pragma unroll
+    for (int j = 0; j < S; ++j) acc = fma(w[j], k[j][c], acc);
+    out[c] = fma(-h, acc, y_end[c]);
+  }
+}
 template <class TB, class F, class T>
 __device__ __forceinline__ void dense_value(const typename F::template ParT<T>& par, double t,
                                             double h, double sigma, const T (&y_end)[F::D],
                                             const T (&y_start)[F::D], T (&k)[TB::S][F::D],
                                             T (&out)[F::D]) {
-  constexpr int S = TB::S, D = F::D;
   if constexpr (TB::POLY_DENSE) {
-    double w[S];
-    sfor<S>([&](auto J) {
-      constexpr int j = decltype(J)::value;
-      double acc = 0.0;
-      rfor<TB::DEG>([&](auto Q) {
-        constexpr int q = decltype(Q)::value;
-        acc = fma(acc, sigma, TB::Bs(j, q));
-      });
-      w[j] = TB::B(j) - acc * sigma;
-    });
-#pragma unroll
-    for (int c = 0; c < D; ++c) {
-      T acc = zero<T>();
-#pragma unroll
-      for (int j = 0; j < S; ++j) acc = fma(w[j], k[j][c], acc);
-      out[c] = fma(-h, acc, y_end[c]);
-    }
+    dense_poly<TB, F::D>(h, sigma, y_end, k, out);
   } else {
     static_assert(!TB::FSAL, "shortened-step outputs reuse the stages of a pair without FSAL");
     rk_stages<TB, F>(par, t, sigma * h, y_start, k, out);
@@ -624,7 +629,8 @@ struct FwdOccupancy {
 // [d][M][n] and S_out [d][M][K][n].  Step control reads values only, so the
 // steps are those of the plain solve.
 struct SensParams {
-  int32_t col[4];      // this launch's columns (template M of them)
+  int32_t col[16];     // this launch's columns
+  int32_t m;           // how many of them (tangent lanes; else template M)
   int32_t m_total;     // columns of the output arrays
   int32_t m0;          // first output column of this launch
   double* S_final;
@@ -688,15 +694,6 @@ __device__ __forceinline__ double row_bcast(double v) {
   return __longlong_as_double(
       __builtin_amdgcn_mov_dpp(__double_as_longlong(v), 0x150 + SRC, 0xF, 0xF, true));
 }
-// The same for a dual number: the value and each tangent.
-template <int SRC, int M>
-__device__ __forceinline__ ad::Dual<M> row_bcast(const ad::Dual<M>& v) {
-  ad::Dual<M> r;
-  r.v = row_bcast<SRC>(v.v);
-#pragma unroll
-  for (int m = 0; m < M; ++m) r.d[m] = row_bcast<SRC>(v.d[m]);
-  return r;
-}
 // Sum of lanes 0..D-1 of the row, in every lane of the row: each value is
 // broadcast and the sum taken in the pairwise order of error_norm2 (pairs,
 // then pairs of pairs, ...), so a group's norm has the bits of one lane's.
@@ -716,8 +713,8 @@ __device__ __forceinline__ double row_sum(double v) {
 }
 
 // Full vector of the row's components (lanes 0..D-1), in every lane.
-template <int D, class T>
-__device__ __forceinline__ void row_gather(const T& v, T (&out)[D]) {
+template <int D>
+__device__ __forceinline__ void row_gather(double v, double (&out)[D]) {
   sfor<D>([&](auto C) {
     constexpr int c = decltype(C)::value;
     out[c] = row_bcast<c>(v);
@@ -735,21 +732,6 @@ __device__ __forceinline__ double pick(const double (&v)[D], int c) {
     r = (r & ~m) | ((unsigned long long)__double_as_longlong(v[j]) & m);
   }
   return __longlong_as_double((long long)r);
-}
-template <int D, int M>
-__device__ __forceinline__ ad::Dual<M> pick(const ad::Dual<M> (&v)[D], int c) {
-  double part[D];
-  ad::Dual<M> r;
-#pragma unroll
-  for (int j = 0; j < D; ++j) part[j] = v[j].v;
-  r.v = pick<D>(part, c);
-#pragma unroll
-  for (int m = 0; m < M; ++m) {
-#pragma unroll
-    for (int j = 0; j < D; ++j) part[j] = v[j].d[m];
-    r.d[m] = pick<D>(part, c);
-  }
-  return r;
 }
 
 // Component c of f(t, Y) for the row whose lane c holds Y[c]: the full
@@ -786,23 +768,6 @@ struct RowRhs<LogHalo> {
     return c < 3 ? vel : s * (w * pos);
   }
 };
-
-// Component c of f for the solve's scalar type: the per-component form of
-// the row for double, and for dual numbers (sensitivity solves) the gathered
-// vector through the ordinary right-hand side, which is exactly the
-// arithmetic of one lane's sensitivity solve.
-template <class F, class T>
-__device__ __forceinline__ T row_f(double t, const T& yc,
-                                   const typename F::template ParT<T>& p, int c) {
-  if constexpr (std::is_same<T, double>::value) {
-    return RowRhs<F>::f(t, yc, p, c);
-  } else {
-    T Y[F::D], kf[F::D];
-    row_gather<F::D>(yc, Y);
-    F::f(t, Y, p, kf);
-    return c < F::D ? pick<F::D>(kf, c) : zero<T>();
-  }
-}
 
 // The tableau's coefficients in vector registers for the group loop.  As
 // immediates every 64-bit coefficient costs two scalar moves per use inside
@@ -842,25 +807,23 @@ struct GroupCoef {
   }
 };
 
-template <class TB, class F, class T = double>
+template <class TB, class F>
 struct GroupTraj {
   static constexpr int S = TB::S, D = F::D;
-  Inputs<F, T> in;
-  T y;     // own component (0 beyond d)
-  T k[S];  // own component of each stage derivative
+  Inputs<F> in;
+  double y;     // own component (0 beyond d)
+  double k[S];  // own component of each stage derivative
   double t, h, err_prev2;
   int32_t nacc, nrej, nanrun;
   int32_t ck_left;  // accepted steps until the next checkpoint
 };
 
-// One attempt of a group: the single-lane attempt() component by component
-// (for a dual scalar type the error estimate and step control read the
-// values only, as one lane's do).  on_accept(t_old, h, y_old) runs on
-// acceptance with the new state in s and the step's stages still in s.k, as
-// in the single-lane attempt.
-template <class TB, class F, class T, class OnAccept>
+// One attempt of a group: the single-lane attempt() component by component.
+// on_accept(t_old, h, y_old) runs on acceptance with the new state in s and
+// the step's stages still in s.k, as in the single-lane attempt.
+template <class TB, class F, class OnAccept>
 __device__ __forceinline__ Attempt group_attempt(const Params& P, const GroupCoef<TB>& cf,
-                                                 GroupTraj<TB, F, T>& s, int c,
+                                                 GroupTraj<TB, F>& s, int c,
                                                  OnAccept&& on_accept) {
   constexpr int S = TB::S, D = F::D;
   Attempt a;
@@ -872,7 +835,7 @@ __device__ __forceinline__ Attempt group_attempt(const Params& P, const GroupCoe
     last = true;
   }
   a.h_used = hh;
-  T yn = zero<T>();
+  double yn = 0.0;
   // The sums over stages in push form: as soon as k_l is known its terms
   // enter the partial sums of every later stage, of the update and of the
   // error estimate.  Each sum still takes its terms in ascending l, as the
@@ -880,10 +843,10 @@ __device__ __forceinline__ Attempt group_attempt(const Params& P, const GroupCoe
   // changes is that only a_{j,j-1} k_{j-1} and the step stand between one
   // stage's right-hand side and the next stage point, and the other terms
   // fill the latency of the evaluation in flight.
-  T accs[S], accb = zero<T>();
-  double e = 0.0;  // the error estimate reads values only
+  double accs[S], accb = 0.0;
+  double e = 0.0;
 #pragma unroll
-  for (int j = 0; j < S; ++j) accs[j] = zero<T>();
+  for (int j = 0; j < S; ++j) accs[j] = 0.0;
   auto push = [&](auto L) {
     constexpr int l = decltype(L)::value;
     sfor<S>([&](auto J) {
@@ -891,19 +854,19 @@ __device__ __forceinline__ Attempt group_attempt(const Params& P, const GroupCoe
       if constexpr (j > l && TB::A(j, l) != 0.0) accs[j] = fma(cf.a[j][l], s.k[l], accs[j]);
     });
     if constexpr (!TB::FSAL && TB::B(l) != 0.0) accb = fma(cf.b[l], s.k[l], accb);
-    if constexpr (TB::E(l) != 0.0) e = fma(cf.e[l], ad::val(s.k[l]), e);
+    if constexpr (TB::E(l) != 0.0) e = fma(cf.e[l], s.k[l], e);
   };
   push(std::integral_constant<int, 0>{});
   sfor<S - 1>([&](auto J1) {
     constexpr int j = decltype(J1)::value + 1;
-    const T Yc = fma(hh, accs[j], s.y);
-    s.k[j] = row_f<F>(s.t + cf.template node<j>() * hh, Yc, s.in.par, c);
+    const double Yc = fma(hh, accs[j], s.y);
+    s.k[j] = RowRhs<F>::f(s.t + cf.template node<j>() * hh, Yc, s.in.par, c);
     if constexpr (TB::FSAL && j == S - 1) yn = Yc;
     push(std::integral_constant<int, j>{});
   });
   if constexpr (!TB::FSAL) yn = fma(hh, accb, s.y);
   e *= hh;
-  const double sc = fma(s.in.rtol, dmax(fabs(ad::val(s.y)), fabs(ad::val(yn))), s.in.atol);
+  const double sc = fma(s.in.rtol, dmax(fabs(s.y), fabs(yn)), s.in.atol);
   const double r = e * fast_rcp1(sc);
   const double en2 = row_sum<D>(r * r) * (1.0 / D);
   const bool finite = (en2 - en2) == 0.0;
@@ -912,15 +875,15 @@ __device__ __forceinline__ Attempt group_attempt(const Params& P, const GroupCoe
   a.accepted = acc;
   const double t_new = last ? s.in.t1 : s.t + hh;
   a.t_new = t_new;
-  const bool fin = row_sum<D>(fma(ad::val(yn), 0.0, 0.0)) == 0.0;
-  const T y_old = s.y;
-  s.y = ad::select(acc, yn, s.y);
+  const bool fin = row_sum<D>(fma(yn, 0.0, 0.0)) == 0.0;
+  const double y_old = s.y;
+  s.y = acc ? yn : s.y;
   s.t = acc ? t_new : s.t;
   if (acc) on_accept(a.t_start, hh, y_old);
   if constexpr (TB::FSAL) {
-    s.k[0] = ad::select(acc, s.k[S - 1], s.k[0]);
+    s.k[0] = acc ? s.k[S - 1] : s.k[0];
   } else {
-    s.k[0] = row_f<F>(s.t, s.y, s.in.par, c);
+    s.k[0] = RowRhs<F>::f(s.t, s.y, s.in.par, c);
   }
   s.err_prev2 = acc ? dmax(en2, 1e-8) : s.err_prev2;
   s.nacc += acc ? 1 : 0;
@@ -939,9 +902,9 @@ __device__ __forceinline__ Attempt group_attempt(const Params& P, const GroupCoe
 // Component of the dense output (eq:dense) of a pair with a dense
 // polynomial, for the group lane that holds this component: the expression
 // and order of dense_value, so the value is that of one lane.
-template <class TB, class T>
-__device__ __forceinline__ T group_dense(double h, double sigma, const T& y_end,
-                                         const T (&k)[TB::S]) {
+template <class TB>
+__device__ __forceinline__ double group_dense(double h, double sigma, double y_end,
+                                              const double (&k)[TB::S]) {
   constexpr int S = TB::S;
   double w[S];
   sfor<S>([&](auto J) {
@@ -953,41 +916,10 @@ __device__ __forceinline__ T group_dense(double h, double sigma, const T& y_end,
     });
     w[j] = TB::B(j) - acc * sigma;
   });
-  T acc = zero<T>();
+  double acc = 0.0;
 #pragma unroll
   for (int j = 0; j < S; ++j) acc = fma(w[j], k[j], acc);
   return fma(-h, acc, y_end);
-}
-
-// Component of a shortened-step output (a pair without a dense
-// polynomial): the step of length hs from (t, y_start) with k[0] =
-// f(t, y_start), as rk_stages takes it for one lane (sums from zero in
-// ascending l, the tableau's own nodes), so the value is that of one lane.
-// Overwrites k[1..s-1], which an accepted step of a pair without FSAL no
-// longer needs.
-template <class TB, class F, class T>
-__device__ __forceinline__ T group_short_step(const typename F::template ParT<T>& par,
-                                              double t, double hs, const T& y_start,
-                                              T (&k)[TB::S], int c) {
-  constexpr int S = TB::S;
-  static_assert(!TB::FSAL, "shortened-step outputs reuse the stages of a pair without FSAL");
-  sfor<S - 1>([&](auto J1) {
-    constexpr int j = decltype(J1)::value + 1;
-    T acc = zero<T>();
-    sfor<j>([&](auto L) {
-      constexpr int l = decltype(L)::value;
-      constexpr double a = TB::A(j, l);
-      if constexpr (a != 0.0) acc = fma(a, k[l], acc);
-    });
-    k[j] = row_f<F>(t + TB::C(j) * hs, fma(hs, acc, y_start), par, c);
-  });
-  T acc = zero<T>();
-  sfor<S>([&](auto J) {
-    constexpr int j = decltype(J)::value;
-    constexpr double b = TB::B(j);
-    if constexpr (b != 0.0) acc = fma(b, k[j], acc);
-  });
-  return fma(hs, acc, y_start);
 }
 
 // The group part of a forward launch: workgroups [0, wide_blocks) take the
@@ -1003,21 +935,14 @@ __device__ __forceinline__ T group_short_step(const typename F::template ParT<T>
 // exact hits directly, the others as deferred records (lane 0 the step's
 // start time and length, lane c component c of its start state), or with
 // INLOOP (a pair with a dense polynomial, no pending array) the dense value.
-// T = ad::Dual<M>: a sensitivity solve (no tape), lane c carrying component
-// c of the value and its M tangents; outputs are evaluated in the loop (the
-// dense value, or Verner 7's shortened step on the group) and the tangents
-// land in S_out and S_final as one lane writes them.
-template <class TB, class F, class T, bool NODES, bool TAPE, bool INLOOP>
-__device__ void solve_group(const Params& P, const SensParams& SP) {
+template <class TB, class F, bool NODES, bool TAPE, bool INLOOP>
+__device__ void solve_group(const Params& P) {
   constexpr int D = F::D;
-  constexpr bool SENS = !std::is_same<T, double>::value;
-  constexpr int M = ad::width<T>::value;
-  static_assert(!(SENS && TAPE), "sensitivity solves keep no tape");
-  constexpr bool DEFER = NODES && !INLOOP && !SENS;
+  constexpr bool DEFER = NODES && !INLOOP;
   const int lane = threadIdx.x & 63;
   const int c = lane & (kGroup - 1);
   const int first = lane & ~(kGroup - 1);  // the group's lane 0
-  GroupTraj<TB, F, T> s;
+  GroupTraj<TB, F> s;
   GroupCoef<TB> cf;
   cf.load();
   int64_t idx = -1, ts = 0;  // trajectory and its tape slot
@@ -1026,29 +951,24 @@ __device__ void solve_group(const Params& P, const SensParams& SP) {
   int kp = 0;                           // next output node
   double t_next = __builtin_inf();      // its time, kept in a register
 
-  auto put_node = [&](int kk, const T& v, double t_start = 0.0, double hs = 0.0) {
+  auto put_node = [&](int kk, double v, double t_start = 0.0, double hs = 0.0) {
     if constexpr (DEFER) {
       double* rec = P.pending + ((int64_t)kk * P.n + idx) * (2 + D);
       if (c == 0) rec[1] = hs;
       if (hs != 0.0) {
         if (c == 0) rec[0] = t_start;
-        if (c < D) rec[2 + c] = ad::val(v);
+        if (c < D) rec[2 + c] = v;
         return;
       }
     }
     if (c < D) {
       P.y_out[P.out_layout ? ((int64_t)kk * P.n + idx) * D + c
-                           : ((int64_t)c * P.K + kk) * P.n + idx] = ad::val(v);
-      if constexpr (SENS) {
-#pragma unroll
-        for (int m = 0; m < M; ++m)
-          SP.S_out[(((int64_t)c * SP.m_total + SP.m0 + m) * P.K + kk) * P.n + idx] = v.d[m];
-      }
+                           : ((int64_t)c * P.K + kk) * P.n + idx] = v;
     }
   };
   auto put_record = [&](int n, double h_in) {
     double* r = P.tape + ((int64_t)ts * P.ckpt_cap + n) * store_record_len<F>();
-    if (c < D) r[2 + c] = ad::val(s.y);
+    if (c < D) r[2 + c] = s.y;
     if (c == 0) {
       r[0] = s.t;
       r[1] = h_in;
@@ -1062,24 +982,15 @@ __device__ void solve_group(const Params& P, const SensParams& SP) {
       r[2] = s.err_prev2;
     }
     if (c < D) {
-      r[3 + c] = ad::val(s.y);
-      r[3 + D + c] = ad::val(s.k[0]);
+      r[3 + c] = s.y;
+      r[3 + D + c] = s.k[0];
     }
   };
   auto finish = [&](int32_t st) {
     if constexpr (NODES) {
-      T nan_v = zero<T>();
-      set_all(nan_v, __builtin_nan(""));
-      for (; kp < P.K; ++kp) put_node(kp, nan_v);
+      for (; kp < P.K; ++kp) put_node(kp, __builtin_nan(""));
     }
-    if (c < D) {
-      P.y_final[(int64_t)c * P.n + idx] = ad::val(s.y);
-      if constexpr (SENS) {
-#pragma unroll
-        for (int m = 0; m < M; ++m)
-          SP.S_final[((int64_t)c * SP.m_total + SP.m0 + m) * P.n + idx] = s.y.d[m];
-      }
-    }
+    if (c < D) P.y_final[(int64_t)c * P.n + idx] = s.y;
     if (c == 0) {
       P.n_acc[idx] = s.nacc;
       P.n_rej[idx] = s.nrej;
@@ -1097,19 +1008,10 @@ __device__ void solve_group(const Params& P, const SensParams& SP) {
     }
     s.nacc = s.nrej = s.nanrun = 0;
     s.err_prev2 = 1.0;
-    Inputs<F> ind;  // the double inputs (the starting-step rule reads values)
     double y0[D];
-    load_inputs<F>(P, i, ind, y0);
-    T yv[D];  // the initial state, seeded for a sensitivity solve
-    if constexpr (SENS) {
-      seed_inputs<F, M>(SP, ind, y0, s.in, yv);
-    } else {
-      s.in = ind;
-#pragma unroll
-      for (int j = 0; j < D; ++j) yv[j] = y0[j];
-    }
+    load_inputs<F>(P, i, s.in, y0);
     s.t = s.in.t0;
-    s.y = c < D ? pick<D>(yv, c) : zero<T>();
+    s.y = c < D ? pick<D>(y0, c) : 0.0;
     bool fin = true;
 #pragma unroll
     for (int j = 0; j < D; ++j) fin = fin && (y0[j] == y0[j]) && (fabs(y0[j]) < __builtin_inf());
@@ -1132,13 +1034,10 @@ __device__ void solve_group(const Params& P, const SensParams& SP) {
       finish(ST_OK);
       return;
     }
-    T f0[D];
-    double f0v[D];
-    F::f(s.t, yv, s.in.par, f0);
-#pragma unroll
-    for (int j = 0; j < D; ++j) f0v[j] = ad::val(f0[j]);
-    s.k[0] = c < D ? pick<D>(f0, c) : zero<T>();
-    s.h = P.h0 > 0.0 ? dmin(P.h0, s.in.t1 - s.in.t0) : initial_step<TB, F>(ind, y0, f0v);
+    double f0[D];
+    F::f(s.t, y0, s.in.par, f0);
+    s.k[0] = c < D ? pick<D>(f0, c) : 0.0;
+    s.h = P.h0 > 0.0 ? dmin(P.h0, s.in.t1 - s.in.t0) : initial_step<TB, F>(s.in, y0, f0);
     s.ck_left = P.ckpt_every;
     if constexpr (TAPE) {
       if (P.ckpt_cap <= 0)
@@ -1181,7 +1080,7 @@ __device__ void solve_group(const Params& P, const SensParams& SP) {
           st = ST_MAX_STEPS;
         } else {
           const Attempt a = group_attempt<TB, F>(
-              P, cf, s, c, [&](double t_old, double hh, const T& y_old) {
+              P, cf, s, c, [&](double t_old, double hh, double y_old) {
                 if constexpr (!NODES) return;
                 while (t_next <= s.t) {
                   const double tq = t_next;
@@ -1192,9 +1091,6 @@ __device__ void solve_group(const Params& P, const SensParams& SP) {
                              TB::POLY_DENSE ? hh : ((tq - t_old) / hh) * hh);
                   } else if constexpr (TB::POLY_DENSE) {
                     put_node(kp, group_dense<TB>(hh, (tq - t_old) / hh, s.y, s.k));
-                  } else {
-                    put_node(kp, group_short_step<TB, F>(s.in.par, t_old,
-                                                         ((tq - t_old) / hh) * hh, y_old, s.k, c));
                   }
                   ++kp;
                   t_next = kp < P.K ? node_time(P, kp, idx) : __builtin_inf();
@@ -1478,7 +1374,7 @@ __global__ void __launch_bounds__(256)
     __attribute__((amdgpu_waves_per_eu(FwdOccupancy<TB, F>::waves, 8))) solve_kernel(Params P) {
   if constexpr (F::D <= kGroup) {
     if ((int)blockIdx.x < P.wide_blocks) {  // uniform per workgroup
-      solve_group<TB, F, double, NODES, TAPE, INLOOP>(P, SensParams{});
+      solve_group<TB, F, NODES, TAPE, INLOOP>(P);
       return;
     }
   }
@@ -1527,18 +1423,345 @@ __global__ void __launch_bounds__(256) short_step_kernel(Params P) {
     P.y_out[P.out_layout ? (kk * P.n + i) * D + c : ((int64_t)c * P.K + kk) * P.n + i] = out[c];
 }
 
-// Forward solve with M sensitivity columns in the same launch.  WIDE: the
-// launch runs the head of the order on 16-lane groups (a variant of its own,
-// so that a launch without groups keeps the single-lane register budget).
+// ---------------------------------------------------------------------------
+// Sensitivities with one lane per vector ("tangent lanes").  A group of G
+// lanes holds one trajectory: lane 0 its state, lane m = 1..G-1 the tangent of
+// one column.  The stage sums, the update and the dense output are linear and
+// the same for every lane, each on its own d-vector; a stage's right-hand side
+// takes the value's stage point from lane 0 and is evaluated in every lane as
+// a dual number with the lane's own tangent, of which lane 0 keeps the value
+// and the others the derivative.  Step control reads lane 0.  The arithmetic
+// is that of the dual-number solve of one lane, so values and tangents are
+// the same bit for bit; a lane holds d (s + 2) doubles instead of
+// d (s + 2) (1 + M), which is what the registers of a wavefront allow for the
+// larger systems.  More than G - 1 columns: `chunks` groups take one
+// trajectory, each its own G - 1 columns.
+
+// Lane 0 of this lane's group, in every lane of the group (G = 2 or 4).
+template <int G>
+__device__ __forceinline__ double first_of_group(double v) {
+  static_assert(G == 2 || G == 4, "groups lie within a quad");
+  return dpp_mov<G == 4 ? 0x00 : 0xA0>(v);
+}
+
+template <class TB, class F>
+struct LaneTraj {
+  static constexpr int S = TB::S, D = F::D;
+  typename F::template ParT<ad::Dual<1>> par;  // the tangent with respect to this lane's column
+  double t1, rtol, atol;
+  double y[D], k[S][D];  // the lane's own vector: the value, or a tangent
+  double t, h, err_prev2;
+  int32_t nacc, nrej, nanrun;
+};
+
+// k = f(t, Y) for lane 0 and its derivative along the lane's tangent for the
+// others; Y is the lane's own vector.
+template <class F, int G>
+__device__ __forceinline__ void lanes_f(double t, const double (&Y)[F::D],
+                                        const typename F::template ParT<ad::Dual<1>>& par,
+                                        bool value_lane, double (&k)[F::D]) {
+  ad::Dual<1> Z[F::D], K[F::D];
+#pragma unroll
+  for (int c = 0; c < F::D; ++c) {
+    Z[c].v = first_of_group<G>(Y[c]);
+    Z[c].d[0] = Y[c];
+  }
+  F::f(t, Z, par, K);
+#pragma unroll
+  for (int c = 0; c < F::D; ++c) k[c] = value_lane ? K[c].v : K[c].d[0];
+}
+
+// rk_stages on the lane's own vector.
+template <class TB, class F, int G>
+__device__ __forceinline__ void lanes_stages(
+    const typename F::template ParT<ad::Dual<1>>& par, double t, double h, bool value_lane,
+    const double (&y)[F::D], double (&k)[TB::S][F::D], double (&yn)[F::D]) {
+  constexpr int S = TB::S, D = F::D;
+  sfor<S - 1>([&](auto J1) {
+    constexpr int j = decltype(J1)::value + 1;
+    double Y[D];
+#pragma unroll
+    for (int c = 0; c < D; ++c) {
+      double acc = 0.0;
+      sfor<j>([&](auto L) {
+        constexpr int l = decltype(L)::value;
+        constexpr double a = TB::A(j, l);
+        if constexpr (a != 0.0) acc = fma(a, k[l][c], acc);
+      });
+      Y[c] = fma(h, acc, y[c]);
+    }
+    lanes_f<F, G>(t + TB::C(j) * h, Y, par, value_lane, k[j]);
+    if constexpr (TB::FSAL && j == S - 1) {
+#pragma unroll
+      for (int c = 0; c < D; ++c) yn[c] = Y[c];
+    }
+  });
+  if constexpr (!TB::FSAL) {
+#pragma unroll
+    for (int c = 0; c < D; ++c) {
+      double acc = 0.0;
+      sfor<S>([&](auto J) {
+        constexpr int j = decltype(J)::value;
+        constexpr double b = TB::B(j);
+        if constexpr (b != 0.0) acc = fma(b, k[j][c], acc);
+      });
+      yn[c] = fma(h, acc, y[c]);
+    }
+  }
+}
+
+// Persistent like the other forward kernels: groups take queue positions
+// [0, n * chunks), position / chunks being the place in the caller's order.
+// Every ballot sits where all lanes of the wave execute it; the lanes of a
+// group always take the same branches.
+template <class TB, class F, int G, bool NODES>
+__device__ __forceinline__ void lanes_body(const Params& P, const SensParams& SP, int64_t n_pos,
+                                           unsigned long long* head) {
+  constexpr int D = F::D, S = TB::S;
+  const int lane = threadIdx.x & 63;
+  const int role = lane & (G - 1);
+  const int first = lane & ~(G - 1);
+  const bool value_lane = role == 0;
+  const int chunks = (SP.m + G - 2) / (G - 1);
+  const unsigned long long n_items = (unsigned long long)n_pos * chunks;
+  const int refill = (P.refill + G - 1) / G;
+  LaneTraj<TB, F> s;
+  int64_t idx = -1;
+  int32_t col = -1, m_out = 0;  // input column of this lane's tangent and its place in S
+  int32_t kp = 0;
+  double t_next = __builtin_inf();
+  bool live = false, queue_empty = false;
+
+  auto put_node = [&](int kk, const double (&v)[D]) {
+#pragma unroll
+    for (int c = 0; c < D; ++c) {
+      if (value_lane)
+        P.y_out[P.out_layout ? ((int64_t)kk * P.n + idx) * D + c
+                             : ((int64_t)c * P.K + kk) * P.n + idx] = v[c];
+      else if (col >= 0)
+        SP.S_out[(((int64_t)c * SP.m_total + m_out) * P.K + kk) * P.n + idx] = v[c];
+    }
+  };
+  auto finish = [&](int32_t st) {
+    if constexpr (NODES) {
+      double nan_v[D];
+#pragma unroll
+      for (int c = 0; c < D; ++c) nan_v[c] = __builtin_nan("");
+      for (; kp < P.K; ++kp) put_node(kp, nan_v);
+    }
+#pragma unroll
+    for (int c = 0; c < D; ++c) {
+      if (value_lane)
+        P.y_final[(int64_t)c * P.n + idx] = s.y[c];
+      else if (col >= 0)
+        SP.S_final[((int64_t)c * SP.m_total + m_out) * P.n + idx] = s.y[c];
+    }
+    if (value_lane) {
+      P.n_acc[idx] = s.nacc;
+      P.n_rej[idx] = s.nrej;
+      P.status[idx] = st;
+    }
+    live = false;
+  };
+  auto start = [&](int64_t i, int chunk) {
+    idx = i;
+    live = true;
+    kp = 0;
+    const int m = chunk * (G - 1) + role - 1;
+    const bool used = !value_lane && m < SP.m;
+    m_out = SP.m0 + (used ? m : 0);
+    col = -1;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) col = (used && q == m) ? SP.col[q] : col;
+    s.nacc = s.nrej = s.nanrun = 0;
+    s.err_prev2 = 1.0;
+    Inputs<F> in;
+    double y0[D];
+    load_inputs<F>(P, i, in, y0);
+    ad::Dual<1> th[F::P];
+#pragma unroll
+    for (int q = 0; q < F::P; ++q) {
+      th[q].v = in.th[q];
+      th[q].d[0] = col == D + q ? 1.0 : 0.0;
+    }
+    s.par = F::prep(th);
+    s.t1 = in.t1;
+    s.rtol = in.rtol;
+    s.atol = in.atol;
+    s.t = in.t0;
+    bool fin = true;
+#pragma unroll
+    for (int c = 0; c < D; ++c) {
+      s.y[c] = value_lane ? y0[c] : (col == c ? 1.0 : 0.0);
+      fin = fin && (y0[c] == y0[c]) && (fabs(y0[c]) < __builtin_inf());
+    }
+    if (!inputs_valid<F>(P, i, in)) {
+      finish(ST_BAD_INPUT);
+      return;
+    }
+    // Nodes at t0 take y0.
+    while (NODES && kp < P.K && node_time(P, kp, i) <= in.t0) {
+      put_node(kp, s.y);
+      ++kp;
+    }
+    if constexpr (NODES) t_next = kp < P.K ? node_time(P, kp, i) : __builtin_inf();
+    if (!fin) {
+      finish(ST_NONFINITE);
+      return;
+    }
+    if (!(in.t1 > in.t0)) {
+      finish(ST_OK);
+      return;
+    }
+    lanes_f<F, G>(s.t, s.y, s.par, value_lane, s.k[0]);
+    if (P.h0 > 0.0) {
+      s.h = dmin(P.h0, in.t1 - in.t0);
+    } else {
+      double f0[D];
+#pragma unroll
+      for (int c = 0; c < D; ++c) f0[c] = first_of_group<G>(s.k[0][c]);
+      s.h = initial_step<TB, F>(in, y0, f0);
+    }
+  };
+
+  for (;;) {
+    if (!queue_empty) {
+      // one bit per idle group (its lane 0)
+      const uint64_t idle = __ballot(!live && value_lane);
+      const int nidle = __popcll(idle);
+      if (nidle >= refill) {
+        unsigned long long base = 0;
+        if (lane == 0) base = atomicAdd(head, (unsigned long long)nidle);
+        base = first_lane(base);
+        if (base + (unsigned long long)nidle >= n_items) queue_empty = true;
+        if (!live) {
+          const uint64_t below = first ? (~0ull >> (64 - first)) : 0ull;
+          const unsigned long long item = base + __popcll(idle & below);
+          if (item < n_items) {
+            const unsigned long long pos = item / chunks;
+            const int64_t id = P.order ? P.order[pos] : (int64_t)pos;
+            if (id >= 0 && id < P.n) start(id, (int)(item - pos * chunks));
+          }
+        }
+      }
+    }
+    if (__ballot(live) == 0) {
+      if (queue_empty) break;
+      continue;
+    }
+    int32_t st = -1;
+    // Finished groups wait here until enough are idle for a refill.
+    const int held = __popcll(__ballot(!live && value_lane));
+    const int leave_at = queue_empty ? 64 / G : refill;
+    for (;;) {
+      if (live && st < 0) {
+        if ((int64_t)s.nacc + s.nrej >= P.max_steps) {
+          st = ST_MAX_STEPS;
+        } else {
+          // attempt() on the group: the value's lane decides, every lane moves
+          const double t_old = s.t;
+          bool last = false;
+          double hh = s.h;
+          if (s.t + hh >= s.t1) {
+            hh = s.t1 - s.t;
+            last = true;
+          }
+          double yn[D];
+          lanes_stages<TB, F, G>(s.par, s.t, hh, value_lane, s.y, s.k, yn);
+          const double en2 = first_of_group<G>(
+              error_norm2<TB, F, double>(hh, s.y, yn, s.k, s.rtol, s.atol));
+          const bool finite = (en2 - en2) == 0.0;
+          const double factor = step_factor<TB>(P, en2, s.err_prev2, finite);
+          const bool acc = finite & (en2 <= 1.0);
+          const double t_new = last ? s.t1 : s.t + hh;
+          constexpr bool KEEP_START = NODES && !TB::POLY_DENSE;
+          double ystart[D];
+          double probe = 0.0;
+#pragma unroll
+          for (int c = 0; c < D; ++c) {
+            if constexpr (KEEP_START) ystart[c] = s.y[c];
+            probe = fma(yn[c], 0.0, probe);
+            s.y[c] = acc ? yn[c] : s.y[c];
+          }
+          const bool fin = first_of_group<G>(probe) == 0.0;
+          s.t = acc ? t_new : s.t;
+          if constexpr (NODES) {
+            if (acc) {
+              while (t_next <= s.t) {
+                const double tq = t_next;
+                if (tq == s.t) {
+                  put_node(kp, s.y);
+                } else {
+                  double out[D];
+                  if constexpr (TB::POLY_DENSE)
+                    dense_poly<TB, D>(hh, (tq - t_old) / hh, s.y, s.k, out);
+                  else
+                    lanes_stages<TB, F, G>(s.par, t_old, ((tq - t_old) / hh) * hh, value_lane,
+                                           ystart, s.k, out);
+                  put_node(kp, out);
+                }
+                ++kp;
+                t_next = kp < P.K ? node_time(P, kp, idx) : __builtin_inf();
+              }
+            }
+          }
+          if constexpr (TB::FSAL) {
+#pragma unroll
+            for (int c = 0; c < D; ++c) s.k[0][c] = acc ? s.k[S - 1][c] : s.k[0][c];
+          } else {
+            lanes_f<F, G>(s.t, s.y, s.par, value_lane, s.k[0]);
+          }
+          s.err_prev2 = acc ? dmax(en2, 1e-8) : s.err_prev2;
+          s.nacc += acc ? 1 : 0;
+          s.nrej += acc ? 0 : 1;
+          s.nanrun = finite ? 0 : s.nanrun + 1;
+          s.h = hh * factor;
+          const bool bad_state = acc & !fin;
+          const bool nan_fail = !finite & (s.nanrun >= 50);
+          const bool done = acc & last;
+          const bool tiny = !done & underflow(s.h, s.t);
+          if (bad_state | nan_fail | done | tiny)
+            st = (bad_state | nan_fail) ? ST_NONFINITE : (tiny ? ST_DT_UNDERFLOW : ST_OK);
+        }
+      }
+      const int done = __popcll(__ballot(live && st >= 0 && value_lane));
+      if (done > 0 && held + done >= leave_at) break;
+    }
+    if (live && st >= 0) finish(st);
+  }
+}
+
+template <class TB, class F, int G, bool NODES>
+__global__ void __launch_bounds__(256) sens_lanes_kernel(Params P, SensParams SP) {
+  lanes_body<TB, F, G, NODES>(P, SP, P.n, P.counters);
+}
+
+// Forward solve with M sensitivity columns in dual numbers, one lane per
+// trajectory.  WIDE: the launch runs the head of the order on tangent lanes
+// (a variant of its own, so that a launch without it keeps its register
+// budget).
 template <class TB, class F, int M, bool NODES, bool WIDE>
 __global__ void __launch_bounds__(256) sens_kernel(Params P, SensParams SP) {
-  if constexpr (WIDE && F::D <= kGroup) {
+  if constexpr (WIDE) {
     if ((int)blockIdx.x < P.wide_blocks) {  // uniform per workgroup
-      solve_group<TB, F, ad::Dual<M>, NODES, false, false>(P, SP);
+      lanes_body<TB, F, M == 1 ? 2 : 4, NODES>(P, SP, P.n_wide, P.counters + 3);
       return;
     }
   }
   forward_body<TB, F, ad::Dual<M>, NODES, false>(P, SP);
+}
+
+// Whether dual numbers with two tangents in one lane fit the registers: the
+// state, its successor and the stages, three doubles for each component (and
+// half as many again where outputs take a second, shortened step).  Beyond
+// 230 doubles the kernels spilled 2 to 4 KB a lane and tangent lanes are
+// faster at every size (precession, Verner 7, 60,000 binaries and 3 columns:
+// 17.4 against 83.6 ms; log halo, Verner 7, 16 outputs, 64,000 orbits: 1.5
+// against 4.9 ms), so those pairs have no dual-number kernel.
+template <class TB, class F>
+__host__ __device__ constexpr bool sens_fits_lane(bool nodes) {
+  const int state = 3 * F::D * (TB::S + 2);
+  return (nodes && !TB::POLY_DENSE ? state + state / 2 : state) <= 230;
 }
 
 // ---------------------------------------------------------------------------
@@ -1772,7 +1995,7 @@ struct RecBuf {
 // Reverse of one step on a 16-lane group (one loss, no output seeds): the
 // single-lane reverse_step component by component.  Lane c holds component
 // c of the state, of the running cotangent and of every stage point and
-// stage cotangent; the right-hand side is evaluated per component (row_f)
+// stage cotangent; the right-hand side is evaluated per component (RowRhs)
 // and its vector-Jacobian product on the gathered stage point and stage
 // cotangent in every lane, which keeps its component of the result and
 // accumulates the same parameter cotangent as every other lane.  Sums run
@@ -1786,7 +2009,7 @@ __device__ __forceinline__ void group_reverse_step(const GroupCoef<TB>& cf, cons
 #pragma unroll
   for (int j = 0; j < S; ++j) Ys[j] = k[j] = 0.0;
   Ys[0] = yc;
-  k[0] = row_f<F>(t, yc, in.par, c);
+  k[0] = RowRhs<F>::f(t, yc, in.par, c);
   sfor<S - 1>([&](auto J1) {
     constexpr int j = decltype(J1)::value + 1;
     if constexpr (stage_feeds_step<TB>(j)) {
@@ -1796,7 +2019,7 @@ __device__ __forceinline__ void group_reverse_step(const GroupCoef<TB>& cf, cons
         if constexpr (TB::A(j, l) != 0.0) acc = fma(cf.a[j][l], k[l], acc);
       });
       Ys[j] = fma(h, acc, yc);
-      if constexpr (j < S - 1) k[j] = row_f<F>(t + cf.template node<j>() * h, Ys[j], in.par, c);
+      if constexpr (j < S - 1) k[j] = RowRhs<F>::f(t + cf.template node<j>() * h, Ys[j], in.par, c);
     }
   });
   double kb[S];

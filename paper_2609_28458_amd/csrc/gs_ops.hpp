@@ -26,6 +26,12 @@ struct Ops {
   // Sensitivity solve with M (1 or 2) columns; grid <= 0 writes the blocks
   // per CU of the variant to *S.occupancy_out instead of launching.
   void (*sens)(const gs::Params&, const gs::SensParams&, int M, int grid, int block, hipStream_t);
+  // Sensitivity solve with S.m columns on tangent lanes, groups of G (2 or 4);
+  // grid <= 0 as for sens.
+  void (*sens_lanes)(const gs::Params&, const gs::SensParams&, int G, int grid, int block,
+                     hipStream_t);
+  // Whether the pair has dual-number kernels (sens), [output nodes].
+  bool sens_dual[2];
   // The deferred shortened-step outputs of a plain solve (P.pending set).
   void (*short_steps)(const gs::Params&, hipStream_t);
   // Bytes of LDS per lane the adjoint uses for the stage points (0 when it
