@@ -182,20 +182,26 @@ typedef struct gs_solve_args {
                             run on 16 lanes each (one state component per
                             lane) in the same launch, for the long tail of
                             uneven ensembles; results are bit-identical to
-                            one lane per trajectory.  0 = none.  Needs the
-                            queue schedule (else GS_ERR_UNSUPPORTED); the
-                            tape (either mode) and output nodes are written
-                            record for record as one lane writes them, and
-                            gs_solve_sens carries its tangents on the same
-                            groups (gs_solve_vjp has a `wide` of its own).
-                            Explicit pairs only.  The groups
+                            one lane per trajectory.  0 = automatic: all of
+                            a small ensemble under the queue schedule (up to
+                            one wavefront of groups per SIMD; the static
+                            schedule never takes groups), else none.  > 0
+                            needs the queue schedule (else
+                            GS_ERR_UNSUPPORTED); the tape (either mode) and
+                            output nodes are written record for record as
+                            one lane writes them.  gs_solve_sens runs the
+                            head on tangent lanes instead (gs_solve_vjp has
+                            a `wide` of its own).  Explicit pairs only.  The groups
                             refill from their own queue; they and the single
                             lanes share the grid (the occupancy limit, or
                             `grid` when given), the single lanes keeping up
                             to half of it, each side at least one
                             workgroup.                                      */
   const int64_t* order;  /* [n] queue order (a permutation of 0..n-1), or
-                            NULL for 0, 1, ..., n-1; gs_solve_vjp takes the
+                            NULL: 0, 1, ..., n-1, or the library's own
+                            longest-first order of a large ensemble of
+                            precessing binaries (results do not depend on
+                            the order); gs_solve_vjp takes the
                             trajectories in the same order.  Device memory,
                             read on the device only: entries outside [0, n)
                             are skipped, and before the solve every status
@@ -259,7 +265,10 @@ void gs_default_args(gs_solve_args* args);
  * for the outputs inside steps (start time, length and start state of the
  * step that passes each), which gs_solve evaluates after the solve kernel
  * (one thread per output: the dense polynomial of the step taken again, or
- * Verner 7's shortened step).
+ * Verner 7's shortened step); and for 16,384 or more precessing binaries room
+ * for the library's own queue order (8 n bytes and
+ * gs_queue_order_workspace_bytes(n)), without which the workspace is accepted
+ * too and trajectories are taken in index order.
  * Returns 0 for an invalid `args`. */
 size_t gs_workspace_bytes(const gs_solve_args* args);
 
@@ -304,12 +313,14 @@ gs_status gs_solve_noalloc(const gs_solve_args* args);
  * larger first; otherwise a built-in model, the logarithm of the number of
  * dynamical times in the span times rtol^(-1/nu) for the pair's order nu,
  * where a dynamical time is (rc + r_E) / v0 for orbits in the logarithmic
- * halo (r_E: the in-plane radius at the orbit's energy, eq:st-scales) and
- * the span itself stands for it otherwise.  Keys are put in descending order
+ * halo (r_E: the in-plane radius at the orbit's energy, eq:st-scales); for
+ * precessing binaries the phase of the faster spin, (4 + 3 max(q, 1/q))
+ * (v0^-3 - v1^-3), takes its place, and the span itself otherwise.  Keys are put in descending order
  * by a counting sort over 65,536 buckets of their range (order within a
  * bucket unspecified; non-finite keys last).  Reads from `args` only rhs,
  * tableau, n, the stream and, for the built-in model, t0, t1, rtol (with
- * their strides) and for the halo y0 and theta.  Writes order [n] (device).
+ * their strides), for the halo y0 and theta, and for binaries theta (the
+ * span stands in if it is NULL).  Writes order [n] (device).
  * Kernels only (no memset, no allocation), so the call can be captured in a
  * graph with the solve.  Workspace: gs_queue_order_workspace_bytes(n),
  * 256-byte aligned, device memory. */
@@ -336,10 +347,12 @@ gs_status gs_solve_vjp(const gs_solve_args* fwd, const gs_vjp_args* vjp);
  * with the same steps, since step control reads the values only).  Outputs
  * S_final [d][M][n] and, when K > 0, S_out [d][M][K][n]: S[c][m] is
  * d y_c / d input_m; for shared theta (theta_stride 0) it is the derivative
- * of each trajectory with respect to the shared value.  Columns run two per
- * launch.  No tape; queue schedule only.  `wide` runs the head of the order
- * on 16-lane groups as for gs_solve, values and tangents bit-identical to
- * one lane per trajectory.  1 <= M <= 16. */
+ * of each trajectory with respect to the shared value.  All columns run in one
+ * launch, one lane per tangent, for small ensembles and for the systems whose
+ * tangents do not fit one lane's registers; otherwise two columns per launch
+ * in one lane, `wide` putting the head of the order on one lane per tangent.
+ * Values and tangents are the same, bit for bit, either way.  No tape; queue
+ * schedule only.  1 <= M <= 16. */
 typedef struct gs_sens_args {
   int32_t M;
   const int32_t* cols;    /* [M], host memory                              */

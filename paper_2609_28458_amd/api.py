@@ -290,7 +290,7 @@ class Launch:
     block: int = 0
     grid: int = 0
     refill: int = 0
-    wide: int = 0
+    wide: int = 0  # 0: automatic (all of a small ensemble on 16-lane groups)
     ckpt_every: int = 0
     ckpt_capacity: int = 0
     max_steps: int = 0

@@ -84,9 +84,42 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct Layout {
   size_t tape_off, tape_bytes, scratch_off, scratch_bytes, adj_off, adj_bytes, pending_off,
-      pending_bytes, slot_off, slot_bytes, total;
+      pending_bytes, slot_off, slot_bytes, total, order_off, with_order;
   int64_t adj_lanes;
 };
+
+// Workspace of gs_queue_order: keys, buckets, histogram, key range.
+struct OrderLayout {
+  size_t key, bucket, hist, range, total;
+};
+OrderLayout order_layout(int64_t n) {
+  OrderLayout L;
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    const size_t at = off;
+    off = align256(off + bytes);
+    return at;
+  };
+  L.key = take((size_t)n * 8);
+  L.bucket = take((size_t)n * 4);
+  L.hist = take((size_t)gs::order::kBuckets * 4);
+  L.range = take(16);
+  L.total = off;
+  return L;
+}
+
+// The library orders an ensemble by itself, longest first, where the caller
+// gives no order, the built-in model ranks the costs well, the costs differ by
+// several times whatever the caller's spans and tolerances, and the solve is
+// long against the order's 0.1 ms: precessing binaries, from the size at
+// which tangent lanes fill the chip.  131,072 binaries from r = 1000 (Verner 7,
+// 3.16e-9): 584 ms in index order, where long binaries start late, against
+// 290 ms; 20,000 with three sensitivities (r = 100) 34.9 against 21.0 ms.
+// Orbits take 0.1 to 16 ms and are left to gs_queue_order.
+constexpr int64_t kAutoOrderMin = 16384;
+bool may_auto_order(const gs_solve_args* a) {
+  return a->rhs == GS_RHS_SPINPREC && a->n >= kAutoOrderMin;
+}
 
 // Outputs of the plain solve of an explicit pair (K > 0) are deferred to the
 // output kernel: pending [K][n][2 + d] doubles.  `defer` false (the
@@ -126,6 +159,12 @@ Layout layout_of(const gs_solve_args* a, bool defer = true) {
   L.slot_off = align256(L.pending_off + L.pending_bytes);
   L.slot_bytes = a->ckpt_every > 0 ? (size_t)a->n * 4 : 0;
   L.total = L.slot_off + L.slot_bytes;
+  // Room for the library's own queue order; a workspace without it is
+  // accepted and the trajectories are then taken in index order.
+  L.order_off = align256(L.total);
+  L.with_order = may_auto_order(a)
+                     ? L.order_off + align256((size_t)a->n * 8) + order_layout(a->n).total
+                     : L.total;
   return L;
 }
 
@@ -275,13 +314,37 @@ const Ops& ops(int rhs, int tab) {
   return table[rhs][tab];
 }
 
+// Lanes per workgroup of an explicit launch that needs `lanes` lanes at once.
+// A few workgroups of four wavefronts run slower than the same wavefronts one
+// to a CU (Verner 7 on 2,000 binaries 5.5 against 3.8 ms, Dopri5 on 2,000
+// orbits 1.11 against 0.97 ms; 20,000 binaries 5.3 against 4.7 ms); from one
+// and a half wavefronts per CU on, workgroups of one wavefront are placed
+// unevenly over the SIMDs (65,536 orbits 1.52 against 1.06 ms).
+int auto_block(int64_t lanes) { return lanes <= (int64_t)96 * num_cus() ? 64 : 256; }
+
+// Trajectories at the head of the order on 16-lane groups: the caller's
+// `wide`, or all of a small ensemble, as many groups as one wavefront per
+// SIMD holds.  A group's attempt takes fewer instructions than a lane's where
+// the right-hand side is a small part of it or is written per component
+// (1,000 orbits with 64 outputs 2.75 -> 1.28 ms, 4,096 binaries 3.4 -> 2.8 ms);
+// quintessence, whose exponentials every lane of a group evaluates, gains
+// only while there are a few wavefronts (16 models 56 -> 46 us, 4,096 models
+// 40 -> 57 us).
+int64_t wide_of(const gs_solve_args* a) {
+  if (a->wide > 0) return std::min<int64_t>(a->wide, a->n);
+  if (a->schedule != GS_SCHED_QUEUE || is_stiff(a)) return 0;
+  const int64_t most = (int64_t)(a->rhs == GS_RHS_QUINT ? 2 : 16) * num_cus();
+  return a->n <= most ? a->n : 0;
+}
+
 // Grid of the forward launch: static mode covers n lanes; the persistent
 // queue mode fills every CU to its occupancy limit (or takes the caller's
 // grid) but never launches more lanes than trajectories.  `limit` is the
 // grid before that last clip: the most workgroups the launch may hold.
-void solve_shape(const gs_solve_args* a, int* grid, int* block, int64_t* limit = nullptr,
-                 bool defer = true) {
-  const int b = a->block > 0 ? a->block : 256;
+void solve_shape(const gs_solve_args* a, int64_t n_wide, int* grid, int* block, int64_t* limit,
+                 bool defer) {
+  const int64_t lanes = n_wide == a->n ? n_wide * gs::kGroup : a->n;
+  const int b = a->block > 0 ? a->block : is_stiff(a) ? 256 : auto_block(lanes);
   const int64_t need = (a->n + b - 1) / b;
   int64_t lim = need;
   if (a->schedule == GS_SCHED_STATIC) {
@@ -302,7 +365,7 @@ void solve_shape(const gs_solve_args* a, int* grid, int* block, int64_t* limit =
     *grid = (int)std::min<int64_t>(lim, need);
   }
   *block = b;
-  if (limit) *limit = lim;
+  *limit = lim;
 }
 
 // Split of a launch with `wide` trajectories on groups of `lanes_each` lanes.
@@ -325,23 +388,75 @@ void wide_split(int64_t n, int64_t n_wide, int block, int lanes_each, int64_t li
   *grid = (int)(w + single);
 }
 
+// The kernels of gs_queue_order (arguments checked, workspace of
+// order_layout(n)).
+void launch_order(const gs_solve_args* a, const double* cost, int64_t* order, char* ws,
+                  hipStream_t s) {
+  const OrderLayout L = order_layout(a->n);
+  gs::order::Ws w;
+  w.key = reinterpret_cast<double*>(ws + L.key);
+  w.bucket = reinterpret_cast<uint32_t*>(ws + L.bucket);
+  w.hist = reinterpret_cast<uint32_t*>(ws + L.hist);
+  w.range = reinterpret_cast<unsigned long long*>(ws + L.range);
+  gs::order::CostIn c;
+  std::memset(&c, 0, sizeof c);
+  c.n = a->n;
+  // The binaries' model needs their mass ratio; without theta the span does.
+  const bool theta_ok = a->theta && (a->theta_stride == 0 || a->theta_stride == a->n);
+  c.model = cost                                          ? gs::order::kSpan
+            : a->rhs == GS_RHS_LOGHALO                    ? gs::order::kLogHalo
+            : a->rhs == GS_RHS_SPINPREC && theta_ok       ? gs::order::kSpinPrec
+                                                          : gs::order::kSpan;
+  c.inv_nu = 1.0 / tab_order(a->tableau);
+  c.y0 = a->y0;
+  c.theta = a->theta;
+  c.theta_stride = a->theta_stride;
+  c.t0 = a->t0;
+  c.t1 = a->t1;
+  c.t_stride = a->t_stride;
+  c.rtol = a->rtol;
+  c.tol_stride = a->tol_stride;
+  c.cost = cost;
+  const int grid = (int)((a->n + 255) / 256);
+  hipLaunchKernelGGL(gs::order::clear_kernel, dim3(gs::order::kBuckets / 256), dim3(256), 0, s,
+                     w);
+  hipLaunchKernelGGL(gs::order::key_kernel, dim3(grid), dim3(256), 0, s, c, w);
+  hipLaunchKernelGGL(gs::order::bucket_kernel, dim3(grid), dim3(256), 0, s, a->n, w);
+  hipLaunchKernelGGL(gs::order::scan_kernel, dim3(1), dim3(gs::order::kScanThreads), 0, s, w);
+  hipLaunchKernelGGL(gs::order::scatter_kernel, dim3(grid), dim3(256), 0, s, a->n, w, order);
+}
+
+// The library's own order in the workspace (see may_auto_order) when the
+// launch cannot hold all trajectories at once, else the caller's (or null).
+const int64_t* queue_order_of(const gs_solve_args* a, bool refills, hipStream_t s) {
+  if (a->order || !refills || !may_auto_order(a) || a->schedule != GS_SCHED_QUEUE) return a->order;
+  const Layout L = layout_of(a);
+  if (a->workspace_bytes < L.with_order) return nullptr;
+  char* ws = static_cast<char*>(a->workspace) + L.order_off;
+  int64_t* order = reinterpret_cast<int64_t*>(ws);
+  launch_order(a, nullptr, order, ws + align256((size_t)a->n * 8), s);
+  return order;
+}
+
 gs_status launch_solve_all(const gs_solve_args* a, bool defer = true) {
   hipStream_t s = static_cast<hipStream_t>(a->stream);
-  const Params P = make_params(a, defer);
-  Params P2 = P;
+  Params P = make_params(a, defer);
+  P.n_wide = wide_of(a);
+  int grid = 0, block = 0;
+  int64_t limit = 0;
+  solve_shape(a, P.n_wide, &grid, &block, &limit, defer);
+  P.order = queue_order_of(a, P.n_wide == 0 && (a->n + block - 1) / block > limit, s);
   hipLaunchKernelGGL(reset_queues_kernel, dim3(1), dim3(64), 0, s, P.counters, (long long)P.n_wide);
   if (a->order)
     hipLaunchKernelGGL(fill_status_kernel, dim3(fill_grid(P.n)), dim3(256), 0, s, P.status, P.n,
                        (int32_t)GS_TRAJ_NOT_RUN);
-  int grid = 0, block = 0;
-  int64_t limit = 0;
-  solve_shape(a, &grid, &block, &limit, defer);
   if (is_stiff(a)) {
     gs_host::launch_stiff(a->rhs, P, grid, block, s);
     return hipGetLastError() == hipSuccess ? GS_OK : GS_ERR_HIP;
   }
-  if (P.n_wide > 0) wide_split(P.n, P.n_wide, block, gs::kGroup, limit, &P2.wide_blocks, &grid);
-  ops(a->rhs, a->tableau).solve(P2, grid, block, s);
+  if (P.n_wide > 0)
+    wide_split(P.n, P.n_wide, block, gs::kGroup, limit, &P.wide_blocks, &grid);
+  ops(a->rhs, a->tableau).solve(P, grid, block, s);
   if (P.pending) ops(a->rhs, a->tableau).short_steps(P, s);
   return hipGetLastError() == hipSuccess ? GS_OK : GS_ERR_HIP;
 }
@@ -374,26 +489,6 @@ gs_status static_scratch(void** out) {
   return GS_OK;
 }
 
-// Workspace of gs_queue_order: keys, buckets, histogram, key range.
-struct OrderLayout {
-  size_t key, bucket, hist, range, total;
-};
-OrderLayout order_layout(int64_t n) {
-  OrderLayout L;
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
-    const size_t at = off;
-    off = align256(off + bytes);
-    return at;
-  };
-  L.key = take((size_t)n * 8);
-  L.bucket = take((size_t)n * 4);
-  L.hist = take((size_t)gs::order::kBuckets * 4);
-  L.range = take(16);
-  L.total = off;
-  return L;
-}
-
 }  // namespace
 
 struct gs_graph {
@@ -419,7 +514,7 @@ size_t gs_workspace_bytes(const gs_solve_args* a) {
   if (!a || a->rhs < 0 || a->rhs >= kNumRhs || a->n < 0 || a->ckpt_every < 0 ||
       a->ckpt_capacity < 0)
     return 0;
-  return layout_of(a).total;
+  return layout_of(a).with_order;
 }
 
 gs_status gs_solve(const gs_solve_args* a) {
@@ -475,34 +570,7 @@ gs_status gs_queue_order(const gs_solve_args* a, const double* cost, int64_t* or
   const OrderLayout L = order_layout(a->n);
   if (!workspace || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < L.total)
     return GS_ERR_WORKSPACE;
-  char* ws = static_cast<char*>(workspace);
-  gs::order::Ws w;
-  w.key = reinterpret_cast<double*>(ws + L.key);
-  w.bucket = reinterpret_cast<uint32_t*>(ws + L.bucket);
-  w.hist = reinterpret_cast<uint32_t*>(ws + L.hist);
-  w.range = reinterpret_cast<unsigned long long*>(ws + L.range);
-  gs::order::CostIn c;
-  std::memset(&c, 0, sizeof c);
-  c.n = a->n;
-  c.loghalo = (!cost && a->rhs == GS_RHS_LOGHALO) ? 1 : 0;
-  c.inv_nu = 1.0 / tab_order(a->tableau);
-  c.y0 = a->y0;
-  c.theta = a->theta;
-  c.theta_stride = a->theta_stride;
-  c.t0 = a->t0;
-  c.t1 = a->t1;
-  c.t_stride = a->t_stride;
-  c.rtol = a->rtol;
-  c.tol_stride = a->tol_stride;
-  c.cost = cost;
-  hipStream_t s = static_cast<hipStream_t>(a->stream);
-  const int grid = (int)((a->n + 255) / 256);
-  hipLaunchKernelGGL(gs::order::clear_kernel, dim3(gs::order::kBuckets / 256), dim3(256), 0, s,
-                     w);
-  hipLaunchKernelGGL(gs::order::key_kernel, dim3(grid), dim3(256), 0, s, c, w);
-  hipLaunchKernelGGL(gs::order::bucket_kernel, dim3(grid), dim3(256), 0, s, a->n, w);
-  hipLaunchKernelGGL(gs::order::scan_kernel, dim3(1), dim3(gs::order::kScanThreads), 0, s, w);
-  hipLaunchKernelGGL(gs::order::scatter_kernel, dim3(grid), dim3(256), 0, s, a->n, w, order);
+  launch_order(a, cost, order, static_cast<char*>(workspace), static_cast<hipStream_t>(a->stream));
   return hipGetLastError() == hipSuccess ? GS_OK : GS_ERR_HIP;
 }
 
@@ -524,7 +592,10 @@ gs_status gs_solve_vjp(const gs_solve_args* fwd, const gs_vjp_args* v) {
   // that would need more than the device allows per workgroup gets fewer
   // lanes.
   const size_t lds_lane = (size_t)ops(fwd->rhs, fwd->tableau).vjp_lds_lane[fwd->K > 0 ? 1 : 0];
-  int block = v->block > 0 ? v->block : 256;
+  // Workgroups of one wavefront up to one per two SIMDs, as in auto_block (2,000
+  // orbits 0.78 against 0.96 ms, 20,000 binaries 17.2 against 19.5 ms, 40,000
+  // binaries 19.9 against 19.5 ms).
+  int block = v->block > 0 ? v->block : fwd->n <= (int64_t)128 * num_cus() ? 64 : 256;
   while (block > 64 && lds_lane * block > max_lds_per_block()) block -= 64;
   if (lds_lane * block > max_lds_per_block()) return GS_ERR_UNSUPPORTED;
   hipStream_t s = static_cast<hipStream_t>(v->stream);
@@ -599,8 +670,11 @@ bool on_tangent_lanes(const gs_solve_args* a, int M, const Ops& o) {
 // The launches of a sensitivity solve whose arguments have been checked.
 void sens_launches(const gs_solve_args* a, const gs_sens_args* sa) {
   hipStream_t s = static_cast<hipStream_t>(a->stream);
-  const Params P = make_params(a);
-  const int block = a->block > 0 ? a->block : 256;
+  Params P = make_params(a);
+  const gs_host::Ops& o = ops(a->rhs, a->tableau);
+  const bool tangent_lanes = on_tangent_lanes(a, sa->M, o);
+  const int64_t lanes = tangent_lanes ? a->n * tangent_lanes_each(sa->M) : a->n;
+  const int block = a->block > 0 ? a->block : auto_block(lanes);
   gs::SensParams S;
   std::memset(&S, 0, sizeof S);
   S.m_total = sa->M;
@@ -609,7 +683,6 @@ void sens_launches(const gs_solve_args* a, const gs_sens_args* sa) {
   if (a->order)
     hipLaunchKernelGGL(fill_status_kernel, dim3(fill_grid(P.n)), dim3(256), 0, s, P.status, P.n,
                        (int32_t)GS_TRAJ_NOT_RUN);
-  const gs_host::Ops& o = ops(a->rhs, a->tableau);
   // The grid's limit: the caller's, or the occupancy of the variant.
   auto limit_of = [&](auto&& query) {
     if (a->grid > 0) return (int64_t)a->grid;
@@ -619,17 +692,17 @@ void sens_launches(const gs_solve_args* a, const gs_sens_args* sa) {
     S.occupancy_out = nullptr;
     return (int64_t)std::max(per_cu, 1) * num_cus();
   };
-  if (on_tangent_lanes(a, sa->M, o)) {
+  if (tangent_lanes) {
     const int G = tangent_group(sa->M);
-    Params P2 = P;
-    P2.n_wide = 0;
+    P.n_wide = 0;
     S.m0 = 0;
     S.m = sa->M;
     for (int m = 0; m < sa->M; ++m) S.col[m] = sa->cols[m];
-    const int64_t need = (a->n * tangent_lanes_each(sa->M) + block - 1) / block;
-    const int64_t limit = limit_of([&] { o.sens_lanes(P2, S, G, 0, block, s); });
+    const int64_t need = (lanes + block - 1) / block;
+    const int64_t limit = limit_of([&] { o.sens_lanes(P, S, G, 0, block, s); });
+    P.order = queue_order_of(a, need > limit, s);
     hipLaunchKernelGGL(reset_queues_kernel, dim3(1), dim3(64), 0, s, P.counters, 0ll);
-    o.sens_lanes(P2, S, G, (int)std::min<int64_t>(limit, need), block, s);
+    o.sens_lanes(P, S, G, (int)std::min<int64_t>(limit, need), block, s);
     return;
   }
   // Two columns per launch; each launch integrates the solution again and
