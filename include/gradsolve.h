@@ -185,7 +185,9 @@ typedef struct gs_solve_args {
                             one lane per trajectory.  0 = automatic: all of
                             a small ensemble under the queue schedule (up to
                             one wavefront of groups per SIMD; the static
-                            schedule never takes groups), else none.  > 0
+                            schedule never takes groups), the longest 512
+                            of orbits the library orders by itself, else
+                            none.  > 0
                             needs the queue schedule (else
                             GS_ERR_UNSUPPORTED); the tape (either mode) and
                             output nodes are written record for record as
@@ -199,8 +201,9 @@ typedef struct gs_solve_args {
                             workgroup.                                      */
   const int64_t* order;  /* [n] queue order (a permutation of 0..n-1), or
                             NULL: 0, 1, ..., n-1, or the library's own
-                            longest-first order of a large ensemble of
-                            precessing binaries (results do not depend on
+                            longest-first order for 16,384 or more binaries
+                            and for as many orbits or binaries with a tape
+                            of 256 steps or more (results do not depend on
                             the order); gs_solve_vjp takes the
                             trajectories in the same order.  Device memory,
                             read on the device only: entries outside [0, n)
@@ -265,10 +268,10 @@ void gs_default_args(gs_solve_args* args);
  * for the outputs inside steps (start time, length and start state of the
  * step that passes each), which gs_solve evaluates after the solve kernel
  * (one thread per output: the dense polynomial of the step taken again, or
- * Verner 7's shortened step); and for 16,384 or more precessing binaries room
- * for the library's own queue order (8 n bytes and
- * gs_queue_order_workspace_bytes(n)), without which the workspace is accepted
- * too and trajectories are taken in index order.
+ * Verner 7's shortened step); and where the library may order the ensemble by
+ * itself (see `order`) room for that order, 8 n bytes and
+ * gs_queue_order_workspace_bytes(n) at the end, without which the workspace is
+ * accepted too and trajectories are taken in index order.
  * Returns 0 for an invalid `args`. */
 size_t gs_workspace_bytes(const gs_solve_args* args);
 

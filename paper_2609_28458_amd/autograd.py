@@ -55,6 +55,7 @@ def _solve_with_tape(prob: api.Problem, spec: SolveSpec) -> api.Solution:
     earlier calls (with a quarter in hand); only a trajectory that overflows
     it makes the forward run again, once, with the capacity it needs."""
     steps = spec.steps_seen + spec.steps_seen // 4 if spec.steps_seen else 256
+    spec.last_solution = None  # its tape's memory serves this call
     while True:
         k, cap = _tape_mode(prob, spec, steps)
         L = api.Launch(**{**spec.launch.__dict__, "ckpt_every": k, "ckpt_capacity": cap})
@@ -64,6 +65,7 @@ def _solve_with_tape(prob: api.Problem, spec: SolveSpec) -> api.Solution:
         if spec.ckpt_capacity or nmax // k + 2 <= cap:
             return sol
         steps = nmax
+        del sol
 
 
 class GsSolveFn(torch.autograd.Function):
@@ -76,12 +78,15 @@ class GsSolveFn(torch.autograd.Function):
         ctx.sol = sol
         ctx.shared_theta = theta.dim() == 1
         ctx.mark_non_differentiable(sol.status)
+        # Outputs share the solution's memory but are other tensors: autograd hangs
+        # this node on what forward returns, and a node that holds its own
+        # outputs is freed by the cycle collector only, tape and all.
         if sol.y_out is not None:
-            y_out = sol.y_out
+            y_out = sol.y_out.detach()
         else:
             y_out = y0.new_zeros((0, prob.n, prob.d) if sol.launch.out_layout == "knd"
                                  else (prob.d, 0, prob.n))
-        return y_out, sol.y_final, sol.status
+        return y_out, sol.y_final.detach(), sol.status
 
     @staticmethod
     def backward(ctx, g_out, g_final, _g_status):

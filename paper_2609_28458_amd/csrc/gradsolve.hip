@@ -109,16 +109,27 @@ OrderLayout order_layout(int64_t n) {
 }
 
 // The library orders an ensemble by itself, longest first, where the caller
-// gives no order, the built-in model ranks the costs well, the costs differ by
-// several times whatever the caller's spans and tolerances, and the solve is
-// long against the order's 0.1 ms: precessing binaries, from the size at
-// which tangent lanes fill the chip.  131,072 binaries from r = 1000 (Verner 7,
-// 3.16e-9): 584 ms in index order, where long binaries start late, against
-// 290 ms; 20,000 with three sensitivities (r = 100) 34.9 against 21.0 ms.
-// Orbits take 0.1 to 16 ms and are left to gs_queue_order.
+// gives no order, the built-in model ranks the costs well, and the solve is
+// long against the order's 0.1 ms, which has to show without reading device
+// memory:
+//  - precessing binaries (any span: their steps cost microseconds and their
+//    costs differ several times) once the launch cannot hold them all, from
+//    the size at which tangent lanes fill the chip.  131,072 binaries from r =
+//    1000 (Verner 7, 3.16e-9): 584 ms in index order, where long binaries
+//    start late, against 290 ms; 20,000 with three sensitivities (r = 100)
+//    34.9 against 21.0 ms;
+//  - orbits and binaries that keep a tape for at least 256 steps: solve and
+//    adjoint both take the order, so that the lanes of a wavefront finish
+//    together (gradient of 100,000 orbits to t = 100: forward with tape and
+//    adjoint 16.1 ms in index order, 10.4 ms).
+// Other orbits take 0.1 to 16 ms and are left to gs_queue_order.
 constexpr int64_t kAutoOrderMin = 16384;
+bool orders_tape(const gs_solve_args* a) {
+  return (a->rhs == GS_RHS_LOGHALO || a->rhs == GS_RHS_SPINPREC) && a->n >= kAutoOrderMin &&
+         a->ckpt_every > 0 && (int64_t)a->ckpt_every * a->ckpt_capacity >= 256;
+}
 bool may_auto_order(const gs_solve_args* a) {
-  return a->rhs == GS_RHS_SPINPREC && a->n >= kAutoOrderMin;
+  return orders_tape(a) || (a->rhs == GS_RHS_SPINPREC && a->n >= kAutoOrderMin);
 }
 
 // Outputs of the plain solve of an explicit pair (K > 0) are deferred to the
@@ -314,6 +325,17 @@ const Ops& ops(int rhs, int tab) {
   return table[rhs][tab];
 }
 
+// Where the library's own order lies in the workspace, or null if the
+// arguments do not call for one (see may_auto_order); `refills`: the launch
+// cannot hold all trajectories at once.
+int64_t* own_order(const gs_solve_args* a, bool refills) {
+  if (a->order || a->schedule != GS_SCHED_QUEUE || !(orders_tape(a) || (refills && may_auto_order(a))))
+    return nullptr;
+  const Layout L = layout_of(a);
+  if (a->workspace_bytes < L.with_order) return nullptr;
+  return reinterpret_cast<int64_t*>(static_cast<char*>(a->workspace) + L.order_off);
+}
+
 // Lanes per workgroup of an explicit launch that needs `lanes` lanes at once.
 // A few workgroups of four wavefronts run slower than the same wavefronts one
 // to a CU (Verner 7 on 2,000 binaries 5.5 against 3.8 ms, Dopri5 on 2,000
@@ -330,11 +352,17 @@ int auto_block(int64_t lanes) { return lanes <= (int64_t)96 * num_cus() ? 64 : 2
 // quintessence, whose exponentials every lane of a group evaluates, gains
 // only while there are a few wavefronts (16 models 56 -> 46 us, 4,096 models
 // 40 -> 57 us).
+//
+// Behind the library's own order of taped orbits the longest 512 take groups:
+// the launch ends with its longest orbit (gradient of 20,000 orbits 8.1 -> 7.3
+// ms, of 100,000 10.8 -> 10.5 ms; 1,024: 7.0 and 10.5 ms).
+constexpr int64_t kOwnHead = 512;
 int64_t wide_of(const gs_solve_args* a) {
   if (a->wide > 0) return std::min<int64_t>(a->wide, a->n);
   if (a->schedule != GS_SCHED_QUEUE || is_stiff(a)) return 0;
   const int64_t most = (int64_t)(a->rhs == GS_RHS_QUINT ? 2 : 16) * num_cus();
-  return a->n <= most ? a->n : 0;
+  if (a->n <= most) return a->n;
+  return a->rhs == GS_RHS_LOGHALO && own_order(a, false) ? kOwnHead : 0;
 }
 
 // Grid of the forward launch: static mode covers n lanes; the persistent
@@ -426,16 +454,13 @@ void launch_order(const gs_solve_args* a, const double* cost, int64_t* order, ch
   hipLaunchKernelGGL(gs::order::scatter_kernel, dim3(grid), dim3(256), 0, s, a->n, w, order);
 }
 
-// The library's own order in the workspace (see may_auto_order) when the
-// launch cannot hold all trajectories at once, else the caller's (or null).
+// The queue order of a forward launch: the caller's, the library's own (built
+// here), or null.
 const int64_t* queue_order_of(const gs_solve_args* a, bool refills, hipStream_t s) {
-  if (a->order || !refills || !may_auto_order(a) || a->schedule != GS_SCHED_QUEUE) return a->order;
-  const Layout L = layout_of(a);
-  if (a->workspace_bytes < L.with_order) return nullptr;
-  char* ws = static_cast<char*>(a->workspace) + L.order_off;
-  int64_t* order = reinterpret_cast<int64_t*>(ws);
-  launch_order(a, nullptr, order, ws + align256((size_t)a->n * 8), s);
-  return order;
+  int64_t* own = own_order(a, refills);
+  if (!own) return a->order;
+  launch_order(a, nullptr, own, reinterpret_cast<char*>(own) + align256((size_t)a->n * 8), s);
+  return own;
 }
 
 gs_status launch_solve_all(const gs_solve_args* a, bool defer = true) {
@@ -600,6 +625,8 @@ gs_status gs_solve_vjp(const gs_solve_args* fwd, const gs_vjp_args* v) {
   if (lds_lane * block > max_lds_per_block()) return GS_ERR_UNSUPPORTED;
   hipStream_t s = static_cast<hipStream_t>(v->stream);
   Params P = make_params(fwd);
+  // The forward's own order still lies in its workspace.
+  if (const int64_t* own = own_order(fwd, false)) P.order = own;
   P.n_wide = std::min<int64_t>(v->wide, fwd->n);  // the adjoint's own groups
   P.wide_blocks = 0;
   VjpParams V;
@@ -655,16 +682,18 @@ int64_t tangent_lanes_each(int M) {
 // dual numbers in one lane.  Tangent lanes evaluate the value's right-hand
 // side once per lane, so they cost about twice the arithmetic, but the
 // columns of a small ensemble then fill SIMDs that would stand idle and the
-// launches do not follow one another.  The line lies where the lanes are one
-// and a half wavefronts per SIMD for each launch they replace (Tsit5 orbits, 2
-// columns: 16,000 orbits 445 against 709 us, 32,000 orbits 737 against 700;
-// 9 columns: 32,000 orbits 1.85 against 3.29 ms, 64,000 orbits 3.25 against
-// 3.22; 1 column: 32,000 orbits 441 against 522 us, 64,000 744 against 509).
+// launches do not follow one another.  Against one launch the line lies at one
+// wavefront per SIMD (Tsit5 orbits, 2 columns: 16,000 orbits 445 against 709
+// us, 24,000 orbits 726 against 697, 32,000 orbits 737 against 700; 1 column:
+// 32,000 orbits 441 against 522 us, 64,000 744 against 509); against several
+// at one and a half for each (9 columns: 32,000 orbits 1.85 against 3.29 ms,
+// 64,000 orbits 3.25 against 3.22).
 // Pairs without dual-number kernels always take tangent lanes.
 bool on_tangent_lanes(const gs_solve_args* a, int M, const Ops& o) {
   if (!o.sens_dual[a->K > 0 ? 1 : 0]) return true;
   const int64_t launches = (M + 1) / 2;
-  return a->n * tangent_lanes_each(M) <= launches * 6 * 64 * (int64_t)num_cus();
+  const int64_t waves_per_cu = launches == 1 ? 4 : launches * 6;
+  return a->n * tangent_lanes_each(M) <= waves_per_cu * 64 * num_cus();
 }
 
 // The launches of a sensitivity solve whose arguments have been checked.

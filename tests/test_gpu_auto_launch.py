@@ -92,3 +92,61 @@ def test_order_of_binaries_follows_the_faster_spin():
     assert api.lib().gs_queue_order(C.byref(a), None, out.data_ptr(), ws.data_ptr(),
                                     ws.numel()) == 0
     assert np.array_equal(np.sort(out.cpu().numpy()), np.arange(n))
+
+
+@pytest.mark.parametrize("k", [1, 8])
+@pytest.mark.parametrize("rhs", ["loghalo", "spinprec"])
+def test_own_order_of_a_tape_changes_no_gradient(rhs, k):
+    """With a tape of 256 steps or more the library orders 16,384 orbits or
+    binaries by itself, forward and adjoint (orbits with the longest on
+    groups): bitwise the gradients of index order, given or for want of room
+    in the workspace."""
+    n = 16_384
+    if rhs == "loghalo":
+        w = {**inputs.orbits_uneven(n, seed=54), "t1": 3.0, "rtol": 1e-6, "atol": 1e-6}
+    else:
+        w = {**inputs.spin_precession(n, seed=54), "t0": 11.0 ** -0.5, "t_out": None}
+    prob = _prob(w, n)
+    L = api.Launch(ckpt_every=k, ckpt_capacity=256 // k)
+    yb = torch.as_tensor(np.random.default_rng(55).normal(size=(1, prob.d, n)), device="cuda")
+    grads = []
+    for how in ("own", "small workspace", "index order"):
+        sol = api.Solution(prob, L)
+        if how == "small workspace":
+            sol.args.workspace_bytes -= 8 * n + 256  # cuts into the order's room at its end
+        elif how == "index order":
+            sol.set_order(np.arange(n))
+        sol.run()
+        grads.append(api.solve_vjp(sol, ybar_final=yb))
+        assert bool((sol.status == 0).all())
+        assert sol.replay_mismatches() == 0
+    for other in grads[1:]:
+        for a, b in zip(grads[0], other):
+            assert torch.equal(a, b)
+
+
+def test_differentiable_solve_frees_its_tape_with_its_outputs():
+    """Nothing keeps a solution (and its tape) alive once the caller's tensors
+    are gone, without the cycle collector; the next call starts by letting go
+    of the latest one."""
+    import gc
+    import weakref
+
+    from paper_2609_28458_amd.autograd import SolveSpec, solve_ad
+
+    w = inputs.orbits_forward(n=64, seed=56)
+    y0 = torch.as_tensor(w["y0"], device="cuda").requires_grad_()
+    th = torch.as_tensor(w["theta"], device="cuda").requires_grad_()
+    spec = SolveSpec(w["rhs"], w["tableau"], 0.0, 2.0, 1e-6, 1e-8, np.array([1.0, 2.0]))
+    gc.disable()
+    try:
+        y_out, y_final, _ = solve_ad(spec, y0, th)
+        first = weakref.ref(spec.last_solution)
+        assert torch.equal(first().y_final, y_final) and not first().y_final.requires_grad
+        (y_out.square().sum() + y_final.sum()).backward()
+        spec.last_solution = None
+        assert first() is not None  # the graph holds it
+        del y_out, y_final
+        assert first() is None
+    finally:
+        gc.enable()
