@@ -261,7 +261,8 @@ Params make_params(const gs_solve_args* a, bool defer = true) {
   P.n_acc = a->n_accepted;
   P.n_rej = a->n_rejected;
   P.status = a->status;
-  P.max_steps = a->max_steps > 0 ? a->max_steps : 10000000;
+  P.max_attempts = (uint32_t)std::min<int64_t>(a->max_steps > 0 ? a->max_steps : 10000000,
+                                               UINT32_MAX);
   P.h0 = a->h0;
   P.safety = a->ctrl.safety;
   P.amin = a->ctrl.alpha_min;

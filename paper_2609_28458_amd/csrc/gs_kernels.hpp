@@ -79,6 +79,19 @@ __device__ __forceinline__ double pow_of(double x, double y) {
     return pow(x, y);
 }
 
+// max(|a|, |b|) in one instruction (dmax of the absolute values takes three and
+// canonicalises).  A NaN in either argument gives the other one's magnitude.
+__device__ __forceinline__ double max_abs(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, |%1|, |%2|" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+// max(x, b) and min(x, b) in one instruction (dmax and dmin take three); a NaN
+// x gives the bound.
+__device__ __forceinline__ double at_least(double x, double b) { return __builtin_fmax(x, b); }
+__device__ __forceinline__ double at_most(double x, double b) { return __builtin_fmin(x, b); }
+
 // Every component of x (value and tangents) set to v.
 __device__ __forceinline__ void set_all(double& x, double v) { x = v; }
 template <int M>
@@ -121,7 +134,7 @@ struct Params {
   int32_t* n_acc;
   int32_t* n_rej;
   int32_t* status;
-  int64_t max_steps;
+  uint32_t max_attempts;  // max_steps, at most 2^32 - 1 (two counts of at most 2^31 - 1 each)
   double h0;
   double safety, amin, amax, beta1, beta2;
   int32_t ckpt_every;
@@ -255,11 +268,23 @@ __device__ __forceinline__ void rk_stages(const typename F::template ParT<T>& pa
 // Square of the scaled RMS norm of eq:errnorm, for e = h sum_j (b_j -
 // bhat_j) k_j.  The square suffices: accept iff it is <= 1, and the
 // controller takes its power directly, so no square root is needed.
+// A finite result means that y+ is finite, so an accepted step needs no test
+// of its own: an infinite component makes its scale infinite (rtol > 0) and
+// the refined reciprocal of that NaN; a NaN one comes from a stage that is not
+// finite, and every stage of the update also enters the error estimate
+// (checked below), which then is not finite either.
+template <class TB>
+__host__ __device__ constexpr bool update_in_error() {
+  for (int j = 0; j < TB::S; ++j)
+    if (TB::B(j) != 0.0 && TB::E(j) == 0.0) return false;
+  return true;
+}
 template <class TB, class F, class T>
 __device__ __forceinline__ double error_norm2(double h, const T (&y)[F::D], const T (&yn)[F::D],
                                               const T (&k)[TB::S][F::D], double rtol,
                                               double atol) {
   constexpr int D = F::D;
+  static_assert(update_in_error<TB>(), "a finite norm must imply a finite update");
   double sq[D];
 #pragma unroll
   for (int c = 0; c < D; ++c) {
@@ -270,7 +295,7 @@ __device__ __forceinline__ double error_norm2(double h, const T (&y)[F::D], cons
       if constexpr (w != 0.0) e = fma(w, ad::val(k[j][c]), e);
     });
     e *= h;
-    const double sc = fma(rtol, dmax(fabs(ad::val(y[c])), fabs(ad::val(yn[c]))), atol);
+    const double sc = fma(rtol, max_abs(ad::val(y[c]), ad::val(yn[c])), atol);
     const double r = e * fast_rcp1(sc);
     sq[c] = r * r;
   }
@@ -413,21 +438,21 @@ template <class TB>
 __device__ __forceinline__ double step_factor(const Params& P, double en2, double err_prev2,
                                               bool finite) {
   double raw;
-  if (P.fast_ctrl) {
-    const double x = dmin(dmax(en2, 1e-30), 1e30);
+  if (__builtin_expect(P.fast_ctrl != 0, 1)) {
+    const double x = at_most(at_least(en2, 1e-30), 1e30);
     raw = P.safety * inv_root<2 * TB::ORDER>(x);
   } else {
     const double b1 = P.beta1 > 0.0 ? P.beta1 : 1.0 / TB::ORDER;
     raw = P.safety * pow_of<TB>(en2, -0.5 * b1);
     if (P.beta2 != 0.0) raw *= pow_of<TB>(err_prev2, 0.5 * P.beta2);
   }
-  raw = (en2 == 0.0) ? P.amax : raw;
-  raw = finite ? raw : P.amin;
-  return dmin(P.amax, dmax(P.amin, raw));
+  // A zero norm gives a factor at the upper bound by itself: the clamped root
+  // (fast_ctrl) or an infinite power.
+  return finite ? at_most(at_least(raw, P.amin), P.amax) : P.amin;
 }
 
 __device__ __forceinline__ bool underflow(double h, double t) {
-  return fabs(h) < 16.0 * 2.220446049250313e-16 * dmax(fabs(t), 1.0);
+  return fabs(h) < 16.0 * 2.220446049250313e-16 * at_least(fabs(t), 1.0);
 }
 
 // Integration state of one lane.
@@ -443,6 +468,13 @@ struct Traj {
   int32_t ck_left;   // accepted steps until the next checkpoint
 };
 
+// Attempts of a lane's trajectory so far (a 32-bit sum and comparison per
+// attempt instead of two sign extensions and a 64-bit sum).
+template <class S>
+__device__ __forceinline__ uint32_t attempts_of(const S& s) {
+  return (uint32_t)s.nacc + (uint32_t)s.nrej;
+}
+
 // Outcome of one attempt.
 struct Attempt {
   bool accepted;
@@ -451,9 +483,8 @@ struct Attempt {
   double t_start, h_used, t_new;
 };
 
-// One step attempt with everything the controller does after it.  The
-// accept/reject update is written as per-lane selects (no divergent
-// branch around the state); only output nodes run under a branch:
+// One step attempt with everything the controller does after it.  Output
+// nodes run under the accept branch:
 // `on_accept(s, t_start, h, y_start)` sees y = y+, t = t_new and the step's
 // stages k (k[0] still f(t_start, y_start)); y_start is only meaningful for
 // shortened-step pairs, whose outputs may overwrite k[1..s-1] (see
@@ -485,50 +516,50 @@ __device__ __forceinline__ Attempt attempt(const Params& P, Traj<TB, F, T>& s,
   // a shortened step, or a deferred output (plain solves).  A dual-number
   // solve of a polynomial pair needs only the end state.
   constexpr bool KEEP_START = !TB::POLY_DENSE || std::is_same<T, double>::value;
+  // Plain solves move the state under the accept branch: 64-bit moves of the
+  // accepting lanes, half the instructions of selects.  Dual numbers, whose
+  // state lies partly in accumulation registers, keep selects (200,000 streams
+  // with two columns: 1.81 ms, against 1.90 with moves), but copy the first
+  // stage under the branch: a select between the two stage arrays placed after
+  // it was turned into a choice between their addresses, which kept the
+  // lane's whole state in scratch memory.
+  constexpr bool MOVES = std::is_same<T, double>::value;
   T ystart[D];
-  double probe = 0.0;  // becomes NaN if any component of y+ is not finite
 #pragma unroll
   for (int c = 0; c < D; ++c) {
     if constexpr (KEEP_START) ystart[c] = s.y[c];
-    probe = fma(ad::val(yn[c]), 0.0, probe);
-    s.y[c] = ad::select(acc, yn[c], s.y[c]);
+    if constexpr (!MOVES) s.y[c] = ad::select(acc, yn[c], s.y[c]);
   }
-  const bool fin = probe == 0.0;
-  s.t = acc ? t_new : s.t;
+  if constexpr (!MOVES) s.t = acc ? t_new : s.t;
   if (acc) {
+    if constexpr (MOVES) {
+#pragma unroll
+      for (int c = 0; c < D; ++c) s.y[c] = yn[c];
+      s.t = t_new;
+      s.err_prev2 = at_least(en2, 1e-8);
+    }
     if constexpr (KEEP_START) {
       on_accept(s, a.t_start, hh, ystart);
     } else {
       on_accept(s, a.t_start, hh, s.y);
     }
-  }
-  if constexpr (TB::FSAL && !std::is_same<T, double>::value) {
-    // For dual numbers the first stage is copied under the accept branch:
-    // a select between the two stage arrays placed after that branch was
-    // turned into a choice between their addresses, which kept the lane's
-    // whole state in scratch memory.
-    if (acc) {
+    if constexpr (TB::FSAL) {
 #pragma unroll
       for (int c = 0; c < D; ++c) s.k[0][c] = s.k[S - 1][c];
     }
-  } else if constexpr (TB::FSAL) {
-#pragma unroll
-    for (int c = 0; c < D; ++c) s.k[0][c] = ad::select(acc, s.k[S - 1][c], s.k[0][c]);
-  } else {
-    // A rejected lane recomputes f at its unchanged (t, y): the same value.
-    F::f(s.t, s.y, s.in.par, s.k[0]);
   }
-  s.err_prev2 = acc ? dmax(en2, 1e-8) : s.err_prev2;
+  if constexpr (!MOVES) s.err_prev2 = acc ? at_least(en2, 1e-8) : s.err_prev2;
+  // A rejected lane recomputes f at its unchanged (t, y): the same value.
+  if constexpr (!TB::FSAL) F::f(s.t, s.y, s.in.par, s.k[0]);
   s.nacc += acc ? 1 : 0;
   s.nrej += acc ? 0 : 1;
   s.nanrun = finite ? 0 : s.nanrun + 1;
   s.h = hh * factor;
-  const bool bad_state = acc & !fin;
   const bool nan_fail = !finite & (s.nanrun >= 50);
   const bool done = acc & last;
   const bool tiny = !done & underflow(s.h, s.t);
-  a.finished = bad_state | nan_fail | done | tiny;
-  a.status = (bad_state | nan_fail) ? ST_NONFINITE : (tiny ? ST_DT_UNDERFLOW : ST_OK);
+  a.finished = nan_fail | done | tiny;
+  a.status = nan_fail ? ST_NONFINITE : (tiny ? ST_DT_UNDERFLOW : ST_OK);
   return a;
 }
 
@@ -753,7 +784,9 @@ struct RowRhs {
 // (row_shr:3), times the lane's weight (1, 1, 1/q^2 for c = 3, 4, 5; 0
 // beyond, so lanes c >= 6 get 0 while the state is finite).  The weight
 // depends only on the lane and the parameters, so the compiler keeps it out
-// of the attempt loop.  Every expression and its order are those of
+// of the attempt loop.  Lanes c < 3 read no position (beyond the row: 0) and
+// lanes c >= 3 no velocity (lanes 6 to 8 hold 0), so one fused multiply-add
+// serves both: x 0 + velocity, or acceleration + 0, each exact.  Every expression and its order are those of
 // LogHalo::f (1 * x is exact), so the result is bit-identical to component
 // c of the full evaluation.
 template <>
@@ -765,7 +798,7 @@ struct RowRhs<LogHalo> {
     const double Dn = fma(z * z, p.iq2, fma(y, y, fma(x, x, p.rc2)));
     const double s = -p.v02 * fast_rcp(Dn);
     const double w = c == 5 ? p.iq2 : (c < 6 ? 1.0 : 0.0);
-    return c < 3 ? vel : s * (w * pos);
+    return fma(s, w * pos, vel);
   }
 };
 
@@ -866,7 +899,7 @@ __device__ __forceinline__ Attempt group_attempt(const Params& P, const GroupCoe
   });
   if constexpr (!TB::FSAL) yn = fma(hh, accb, s.y);
   e *= hh;
-  const double sc = fma(s.in.rtol, dmax(fabs(s.y), fabs(yn)), s.in.atol);
+  const double sc = fma(s.in.rtol, max_abs(s.y, yn), s.in.atol);
   const double r = e * fast_rcp1(sc);
   const double en2 = row_sum<D>(r * r) * (1.0 / D);
   const bool finite = (en2 - en2) == 0.0;
@@ -875,7 +908,6 @@ __device__ __forceinline__ Attempt group_attempt(const Params& P, const GroupCoe
   a.accepted = acc;
   const double t_new = last ? s.in.t1 : s.t + hh;
   a.t_new = t_new;
-  const bool fin = row_sum<D>(fma(yn, 0.0, 0.0)) == 0.0;
   const double y_old = s.y;
   s.y = acc ? yn : s.y;
   s.t = acc ? t_new : s.t;
@@ -885,17 +917,16 @@ __device__ __forceinline__ Attempt group_attempt(const Params& P, const GroupCoe
   } else {
     s.k[0] = RowRhs<F>::f(s.t, s.y, s.in.par, c);
   }
-  s.err_prev2 = acc ? dmax(en2, 1e-8) : s.err_prev2;
+  s.err_prev2 = acc ? at_least(en2, 1e-8) : s.err_prev2;
   s.nacc += acc ? 1 : 0;
   s.nrej += acc ? 0 : 1;
   s.nanrun = finite ? 0 : s.nanrun + 1;
   s.h = hh * factor;
-  const bool bad_state = acc & !fin;
   const bool nan_fail = !finite & (s.nanrun >= 50);
   const bool done = acc & last;
   const bool tiny = !done & underflow(s.h, s.t);
-  a.finished = bad_state | nan_fail | done | tiny;
-  a.status = (bad_state | nan_fail) ? ST_NONFINITE : (tiny ? ST_DT_UNDERFLOW : ST_OK);
+  a.finished = nan_fail | done | tiny;
+  a.status = nan_fail ? ST_NONFINITE : (tiny ? ST_DT_UNDERFLOW : ST_OK);
   return a;
 }
 
@@ -1076,7 +1107,7 @@ __device__ void solve_group(const Params& P) {
     int32_t st = -1;
     for (;;) {
       if (live) {
-        if ((int64_t)s.nacc + s.nrej >= P.max_steps) {
+        if (__builtin_expect(attempts_of(s) >= P.max_attempts, 0)) {
           st = ST_MAX_STEPS;
         } else {
           const Attempt a = group_attempt<TB, F>(
@@ -1281,7 +1312,7 @@ __device__ __forceinline__ void forward_body(const Params& P, const SensParams& 
   }
 
   // Outer loop: bookkeeping (retire, refill).  Inner loop: step attempts of
-  // the live lanes until one of them finishes, so the hot loop holds only
+  // the live lanes until enough have finished, so the hot loop holds only
   // the attempt and the rare output and checkpoint writes.
   for (;;) {
     if (!queue_empty) {
@@ -1306,9 +1337,14 @@ __device__ __forceinline__ void forward_body(const Params& P, const SensParams& 
       continue;
     }
     int32_t st = -1;  // status once this lane's trajectory has finished
+    // A finished lane waits in the inner loop until enough lanes are idle for
+    // a refill (all of them once the queue is empty), so its results and the
+    // work around the inner loop are taken once per refill, not per lane.
+    const int held = __popcll(__ballot(!live));
+    const int leave_at = queue_empty ? 64 : P.refill;
     for (;;) {
-      if (live) {
-        if ((int64_t)s.nacc + s.nrej >= P.max_steps) {
+      if (live && st < 0) {
+        if (__builtin_expect(attempts_of(s) >= P.max_attempts, 0)) {
           st = ST_MAX_STEPS;
         } else {
           const Attempt a = attempt<TB, F>(
@@ -1358,7 +1394,8 @@ __device__ __forceinline__ void forward_body(const Params& P, const SensParams& 
           if (a.finished) st = a.status;
         }
       }
-      if (__ballot(live && st >= 0) != 0) break;
+      const int done = __popcll(__ballot(live && st >= 0));
+      if (done > 0 && held + done >= leave_at) break;
     }
     if (live && st >= 0) finish(st);
   }
@@ -1655,7 +1692,7 @@ __device__ __forceinline__ void lanes_body(const Params& P, const SensParams& SP
     const int leave_at = queue_empty ? 64 / G : refill;
     for (;;) {
       if (live && st < 0) {
-        if ((int64_t)s.nacc + s.nrej >= P.max_steps) {
+        if (__builtin_expect(attempts_of(s) >= P.max_attempts, 0)) {
           st = ST_MAX_STEPS;
         } else {
           // attempt() on the group: the value's lane decides, every lane moves
@@ -1676,14 +1713,11 @@ __device__ __forceinline__ void lanes_body(const Params& P, const SensParams& SP
           const double t_new = last ? s.t1 : s.t + hh;
           constexpr bool KEEP_START = NODES && !TB::POLY_DENSE;
           double ystart[D];
-          double probe = 0.0;
 #pragma unroll
           for (int c = 0; c < D; ++c) {
             if constexpr (KEEP_START) ystart[c] = s.y[c];
-            probe = fma(yn[c], 0.0, probe);
             s.y[c] = acc ? yn[c] : s.y[c];
           }
-          const bool fin = first_of_group<G>(probe) == 0.0;
           s.t = acc ? t_new : s.t;
           if constexpr (NODES) {
             if (acc) {
@@ -1711,17 +1745,16 @@ __device__ __forceinline__ void lanes_body(const Params& P, const SensParams& SP
           } else {
             lanes_f<F, G>(s.t, s.y, s.par, value_lane, s.k[0]);
           }
-          s.err_prev2 = acc ? dmax(en2, 1e-8) : s.err_prev2;
+          s.err_prev2 = acc ? at_least(en2, 1e-8) : s.err_prev2;
           s.nacc += acc ? 1 : 0;
           s.nrej += acc ? 0 : 1;
           s.nanrun = finite ? 0 : s.nanrun + 1;
           s.h = hh * factor;
-          const bool bad_state = acc & !fin;
           const bool nan_fail = !finite & (s.nanrun >= 50);
           const bool done = acc & last;
           const bool tiny = !done & underflow(s.h, s.t);
-          if (bad_state | nan_fail | done | tiny)
-            st = (bad_state | nan_fail) ? ST_NONFINITE : (tiny ? ST_DT_UNDERFLOW : ST_OK);
+          if (nan_fail | done | tiny)
+            st = nan_fail ? ST_NONFINITE : (tiny ? ST_DT_UNDERFLOW : ST_OK);
         }
       }
       const int done = __popcll(__ballot(live && st >= 0 && value_lane));
@@ -2251,7 +2284,7 @@ __global__ void __launch_bounds__(256) vjp_kernel(Params P, VjpParams V) {
       bool lost = false;  // the replay ended before m steps: not faithful
       while (__ballot(live && j < m && !lost) != 0) {
         // The forward's step limit bounds a replay that is not faithful.
-        lost = lost | (live && j < m && (int64_t)s.nacc + s.nrej >= P.max_steps);
+        lost = lost | (live && j < m && attempts_of(s) >= P.max_attempts);
         if (live && j < m && !lost) {
           double* rec = scr + (int64_t)j * SREC * 64;
           rec[0] = s.t;

@@ -604,7 +604,7 @@ __device__ __forceinline__ double rodas_attempt(const Inputs<F>& in, double t, d
   double sq = 0.0;
 #pragma unroll
   for (int c = 0; c < D; ++c) {
-    const double sc = fma(in.rtol, dmax(fabs(y[c]), fabs(yn[c])), in.atol);
+    const double sc = fma(in.rtol, max_abs(y[c], yn[c]), in.atol);
     const double r = err[c] * fast_rcp1(sc);
     sq = fma(r, r, sq);
   }
@@ -715,7 +715,7 @@ stiff_kernel(Params P) {
     const int leave_at = queue_empty ? 64 : P.refill;
     for (;;) {
       if (live && st < 0) {
-        if ((int64_t)nacc + nrej >= P.max_steps) {
+        if ((uint32_t)nacc + (uint32_t)nrej >= P.max_attempts) {
           st = ST_MAX_STEPS;
         } else {
           const double stop = t_stop;
