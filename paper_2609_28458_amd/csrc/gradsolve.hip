@@ -844,6 +844,7 @@ gs_status gs_de_profile(const gs_de_profile_args* A) {
   const int blk = 256;
   const int grd = (int)((n + blk - 1) / blk);
   const int grd3 = (int)((3 * n + blk - 1) / blk);
+  const unsigned grd_gn = (unsigned)((n * gs::de::kNodeLanes + blk - 1) / blk);
   hipStream_t s = static_cast<hipStream_t>(A->stream);
   hipLaunchKernelGGL(de_setup_kernel, dim3(grd3), dim3(blk), 0, s, n, D(L.scal), A->N_start,
                      A->rtol, A->atol, D(L.y0));
@@ -918,14 +919,14 @@ gs_status gs_de_profile(const gs_de_profile_args* A) {
     sens_launches(&a, &both);
     g.update = 1;
     g.dist = nullptr;
-    hipLaunchKernelGGL(gs::de::gn_kernel, dim3(grd), dim3(blk), 0, s, g);
+    hipLaunchKernelGGL(gs::de::gn_kernel, dim3(grd_gn), dim3(blk), 0, s, g);
   }
   // chi2 and distances at the returned parameters, the amplitude flat there
   shoot();
   sens_launches(&a, &both);
   g.update = 0;
   g.dist = A->dist;
-  hipLaunchKernelGGL(gs::de::gn_kernel, dim3(grd), dim3(blk), 0, s, g);
+  hipLaunchKernelGGL(gs::de::gn_kernel, dim3(grd_gn), dim3(blk), 0, s, g);
   hipLaunchKernelGGL(gs::de::finish_kernel, dim3(grd), dim3(blk), 0, s, n, D(L.theta), A->a0,
                      A->omega_m);
   return hipGetLastError() == hipSuccess ? GS_OK : GS_ERR_HIP;
