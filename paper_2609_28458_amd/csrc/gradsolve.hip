@@ -283,6 +283,7 @@ Params make_params(const gs_solve_args* a, bool defer = true) {
   P.sched_static = a->schedule == GS_SCHED_STATIC ? 1 : 0;
   P.n_wide = std::min<int64_t>(a->wide, a->n);
   P.wide_blocks = 0;  // set with the launch shape
+  P.placed = 0;       // likewise
   P.fast_ctrl = fast_controller_exact(a) ? 1 : 0;
   return P;
 }
@@ -464,15 +465,33 @@ const int64_t* queue_order_of(const gs_solve_args* a, bool refills, hipStream_t 
   return own;
 }
 
+// Most outputs per trajectory that a small launch of groups evaluates in the
+// loop (a pair with a dense polynomial).  An output then holds its wavefront
+// for about 0.1 us; deferred outputs cost one launch more, about 5 us
+// (quintessence, 16 models with 7 outputs 42.6 us, 40.6 in the loop; 500 models
+// with 8 outputs 44.3 and 42.5, with 64 outputs 71 and 92).  The values are the same bit for bit.
+constexpr int kInLoopNodes = 8;
+
 gs_status launch_solve_all(const gs_solve_args* a, bool defer = true) {
   hipStream_t s = static_cast<hipStream_t>(a->stream);
+  const int64_t n_wide = wide_of(a);
+  if (n_wide == a->n && a->K <= kInLoopNodes && a->ckpt_every == 0) defer = false;
   Params P = make_params(a, defer);
-  P.n_wide = wide_of(a);
+  P.n_wide = n_wide;
   int grid = 0, block = 0;
   int64_t limit = 0;
   solve_shape(a, P.n_wide, &grid, &block, &limit, defer);
   P.order = queue_order_of(a, P.n_wide == 0 && (a->n + block - 1) / block > limit, s);
-  hipLaunchKernelGGL(reset_queues_kernel, dim3(1), dim3(64), 0, s, P.counters, (long long)P.n_wide);
+  if (P.n_wide > 0)
+    wide_split(P.n, P.n_wide, block, gs::kGroup, limit, &P.wide_blocks, &grid);
+  // A launch of groups that holds every trajectory at once needs no queue: 16
+  // models 44.4 -> 42.6 us without the launch that resets it and the reads of
+  // its head.
+  P.placed = a->ckpt_every == 0 && P.n_wide == P.n &&
+             (int64_t)P.wide_blocks * block >= P.n * gs::kGroup;
+  if (!P.placed)
+    hipLaunchKernelGGL(reset_queues_kernel, dim3(1), dim3(64), 0, s, P.counters,
+                       (long long)P.n_wide);
   if (a->order)
     hipLaunchKernelGGL(fill_status_kernel, dim3(fill_grid(P.n)), dim3(256), 0, s, P.status, P.n,
                        (int32_t)GS_TRAJ_NOT_RUN);
@@ -480,8 +499,6 @@ gs_status launch_solve_all(const gs_solve_args* a, bool defer = true) {
     gs_host::launch_stiff(a->rhs, P, grid, block, s);
     return hipGetLastError() == hipSuccess ? GS_OK : GS_ERR_HIP;
   }
-  if (P.n_wide > 0)
-    wide_split(P.n, P.n_wide, block, gs::kGroup, limit, &P.wide_blocks, &grid);
   ops(a->rhs, a->tableau).solve(P, grid, block, s);
   if (P.pending) ops(a->rhs, a->tableau).short_steps(P, s);
   return hipGetLastError() == hipSuccess ? GS_OK : GS_ERR_HIP;
@@ -731,7 +748,9 @@ void sens_launches(const gs_solve_args* a, const gs_sens_args* sa) {
     const int64_t need = (lanes + block - 1) / block;
     const int64_t limit = limit_of([&] { o.sens_lanes(P, S, G, 0, block, s); });
     P.order = queue_order_of(a, need > limit, s);
-    hipLaunchKernelGGL(reset_queues_kernel, dim3(1), dim3(64), 0, s, P.counters, 0ll);
+    P.placed = need <= limit;
+    if (!P.placed)
+      hipLaunchKernelGGL(reset_queues_kernel, dim3(1), dim3(64), 0, s, P.counters, 0ll);
     o.sens_lanes(P, S, G, (int)std::min<int64_t>(limit, need), block, s);
     return;
   }

@@ -10,13 +10,26 @@ namespace gs_host {
 template <class TB, class F>
 void launch_solve(const gs::Params& P, int grid, int block, hipStream_t s) {
   if constexpr (TB::POLY_DENSE) {
-    // Outputs without a pending array (the no-allocation entry point, which
-    // keeps no tape either) are evaluated in the loop.
+    // Outputs without a pending array (the no-allocation entry point and small
+    // launches with few outputs, neither of which keeps a tape) are evaluated
+    // in the loop.
     if (P.K > 0 && !P.pending) {
-      hipLaunchKernelGGL((gs::solve_kernel<TB, F, true, false, true>), dim3(grid), dim3(block), 0,
-                         s, P);
+      if (P.placed)
+        hipLaunchKernelGGL((gs::placed_groups_kernel<TB, F, true, true>), dim3(grid), dim3(block),
+                           0, s, P);
+      else
+        hipLaunchKernelGGL((gs::solve_kernel<TB, F, true, false, true>), dim3(grid), dim3(block),
+                           0, s, P);
       return;
     }
+  }
+  if (P.placed) {
+    if (P.K > 0)
+      hipLaunchKernelGGL((gs::placed_groups_kernel<TB, F, true>), dim3(grid), dim3(block), 0, s, P);
+    else
+      hipLaunchKernelGGL((gs::placed_groups_kernel<TB, F, false>), dim3(grid), dim3(block), 0, s,
+                         P);
+    return;
   }
   if (P.K > 0) {
     if (P.ckpt_every > 0)
