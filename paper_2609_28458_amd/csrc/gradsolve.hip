@@ -348,12 +348,11 @@ int auto_block(int64_t lanes) { return lanes <= (int64_t)96 * num_cus() ? 64 : 2
 
 // Trajectories at the head of the order on 16-lane groups: the caller's
 // `wide`, or all of a small ensemble, as many groups as one wavefront per
-// SIMD holds.  A group's attempt takes fewer instructions than a lane's where
-// the right-hand side is a small part of it or is written per component
-// (1,000 orbits with 64 outputs 2.75 -> 1.28 ms, 4,096 binaries 3.4 -> 2.8 ms);
-// quintessence, whose exponentials every lane of a group evaluates, gains
-// only while there are a few wavefronts (16 models 56 -> 46 us, 4,096 models
-// 40 -> 57 us).
+// SIMD holds.  A group's attempt takes fewer instructions than a lane's
+// (1,000 orbits with 64 outputs 1.04 ms against 2.17 on one lane each, 4,096
+// binaries from r = 100 8.3 against 9.7, 4,096 quintessence models with 7
+// outputs 43 us against 52); with twice as many groups two wavefronts share a
+// SIMD (8,192 models 69 us against 53).
 //
 // Behind the library's own order of taped orbits the longest 512 take groups:
 // the launch ends with its longest orbit (gradient of 20,000 orbits 8.1 -> 7.3
@@ -362,8 +361,7 @@ constexpr int64_t kOwnHead = 512;
 int64_t wide_of(const gs_solve_args* a) {
   if (a->wide > 0) return std::min<int64_t>(a->wide, a->n);
   if (a->schedule != GS_SCHED_QUEUE || is_stiff(a)) return 0;
-  const int64_t most = (int64_t)(a->rhs == GS_RHS_QUINT ? 2 : 16) * num_cus();
-  if (a->n <= most) return a->n;
+  if (a->n <= (int64_t)16 * num_cus()) return a->n;
   return a->rhs == GS_RHS_LOGHALO && own_order(a, false) ? kOwnHead : 0;
 }
 
