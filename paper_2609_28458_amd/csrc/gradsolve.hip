@@ -44,8 +44,24 @@ __global__ void reset_vjp_queues_kernel(unsigned long long* c, long long n_wide)
   if (threadIdx.x == 1) c[3] = 0ull;
 }
 // Forward queue heads: single lanes start after the wide head of the order.
-__global__ void reset_queues_kernel(unsigned long long* c, long long n_wide) {
+// kOrderMark says where this forward built the library's own order (the
+// offset in the workspace; 0: it built none), for an adjoint that follows.
+constexpr int kOrderMark = 4;
+__global__ void reset_queues_kernel(unsigned long long* c, long long n_wide,
+                                    unsigned long long order_at) {
   if (threadIdx.x < 4) c[threadIdx.x] = threadIdx.x == 0 ? (unsigned long long)n_wide : 0ull;
+  if (threadIdx.x == 0) c[kOrderMark] = order_at;
+}
+// Index order where the forward left none at `order_at`: it took a caller's
+// order, the static schedule or a smaller workspace, so the place holds
+// whatever was there before.  A tape serves an adjoint in any order (records
+// are found by the trajectory's slot), so index order is right then.
+__global__ void __launch_bounds__(256) index_order_kernel(const unsigned long long* c,
+                                                          unsigned long long order_at,
+                                                          int64_t* order, int64_t n) {
+  if (c[kOrderMark] == order_at) return;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) order[i] = i;
 }
 
 // Marks every trajectory as not run before a solve with a caller-given queue
@@ -487,9 +503,13 @@ gs_status launch_solve_all(const gs_solve_args* a, bool defer = true) {
   // its head.
   P.placed = a->ckpt_every == 0 && P.n_wide == P.n &&
              (int64_t)P.wide_blocks * block >= P.n * gs::kGroup;
+  // Without a caller's order, P.order is the library's own if there is one.
+  const unsigned long long order_at =
+      P.order && !a->order ? (unsigned long long)((const char*)P.order - (const char*)a->workspace)
+                           : 0ull;
   if (!P.placed)
     hipLaunchKernelGGL(reset_queues_kernel, dim3(1), dim3(64), 0, s, P.counters,
-                       (long long)P.n_wide);
+                       (long long)P.n_wide, order_at);
   if (a->order)
     hipLaunchKernelGGL(fill_status_kernel, dim3(fill_grid(P.n)), dim3(256), 0, s, P.status, P.n,
                        (int32_t)GS_TRAJ_NOT_RUN);
@@ -641,8 +661,12 @@ gs_status gs_solve_vjp(const gs_solve_args* fwd, const gs_vjp_args* v) {
   if (lds_lane * block > max_lds_per_block()) return GS_ERR_UNSUPPORTED;
   hipStream_t s = static_cast<hipStream_t>(v->stream);
   Params P = make_params(fwd);
-  // The forward's own order still lies in its workspace.
-  if (const int64_t* own = own_order(fwd, false)) P.order = own;
+  // The forward's own order still lies in its workspace, if it built one.
+  if (int64_t* own = own_order(fwd, false)) {
+    P.order = own;
+    hipLaunchKernelGGL(index_order_kernel, dim3(fill_grid(P.n)), dim3(256), 0, s, P.counters,
+                       (unsigned long long)L.order_off, own, P.n);
+  }
   P.n_wide = std::min<int64_t>(v->wide, fwd->n);  // the adjoint's own groups
   P.wide_blocks = 0;
   VjpParams V;
@@ -748,7 +772,8 @@ void sens_launches(const gs_solve_args* a, const gs_sens_args* sa) {
     P.order = queue_order_of(a, need > limit, s);
     P.placed = need <= limit;
     if (!P.placed)
-      hipLaunchKernelGGL(reset_queues_kernel, dim3(1), dim3(64), 0, s, P.counters, 0ll);
+      hipLaunchKernelGGL(reset_queues_kernel, dim3(1), dim3(64), 0, s, P.counters, 0ll,
+                         0ull);
     o.sens_lanes(P, S, G, (int)std::min<int64_t>(limit, need), block, s);
     return;
   }
@@ -767,7 +792,7 @@ void sens_launches(const gs_solve_args* a, const gs_sens_args* sa) {
     if (P.n_wide > 0)
       wide_split(P.n, P.n_wide, block, tangent_group(mm), limit, &P2.wide_blocks, &grid);
     hipLaunchKernelGGL(reset_queues_kernel, dim3(1), dim3(64), 0, s, P.counters,
-                       (long long)P.n_wide);
+                       (long long)P.n_wide, 0ull);
     o.sens(P2, S, mm, grid, block, s);
   }
 }
