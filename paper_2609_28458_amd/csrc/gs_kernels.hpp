@@ -467,9 +467,9 @@ __device__ __forceinline__ double step_factor(const Params& P, double en2, doubl
     const double b1 = P.beta1 > 0.0 ? P.beta1 : 1.0 / TB::ORDER;
     raw = P.safety * pow_of<TB>(en2, -0.5 * b1);
     if (P.beta2 != 0.0) raw *= pow_of<TB>(err_prev2, 0.5 * P.beta2);
+    // An infinite power times a vanished one is no number.
+    raw = (en2 == 0.0) ? P.amax : raw;
   }
-  // A zero norm gives a factor at the upper bound by itself: the clamped root
-  // (fast_ctrl) or an infinite power.
   return finite ? at_most(at_least(raw, P.amin), P.amax) : P.amin;
 }
 
