@@ -327,6 +327,8 @@ class Solution:
         self.n_rejected = torch.empty(n, dtype=torch.int32, device=dev)
         self.status = torch.empty(n, dtype=torch.int32, device=dev)
         self.order = None
+        # the stream whose memory the buffers are
+        self._made_on = torch.cuda.current_stream(dev).cuda_stream if dev.type == "cuda" else None
         self.args = self._args()
         nbytes = gs_workspace_bytes(self.args)
         # 256-byte alignment is guaranteed by torch's caching allocator.
@@ -405,6 +407,20 @@ class Solution:
         self.args.stream = _stream_handle(stream)
         gs_solve(self.args)
         return self
+
+    def _in_use_on(self, stream=None):
+        """What a call on `stream` still reads here is not handed out again before
+        that call has ended, also if this solution goes first: its memory belongs
+        to the stream it was made on.  (Autograd lets go of a solution with its
+        graph, and of the latest one when the next solve starts.)"""
+        s = stream if stream is not None else torch.cuda.current_stream()
+        if s.cuda_stream == self._made_on:
+            return
+        p = self.prob
+        for t in (self.workspace, self.y_final, self.n_accepted, self.status, self.order, p.y0,
+                  p.theta, p.t0, p.t1, p.rtol, p.atol, p.t_out):
+            if t is not None and t.is_cuda:
+                t.record_stream(s)
 
     def replay_mismatches(self) -> int:
         """Adjoint segment replays that did not reproduce the next checkpoint."""
@@ -519,6 +535,7 @@ def solve_vjp(sol: Solution, ybar_final=None, ybar_out=None, block=0, grid=0, st
     v = gs_vjp_args(R, _ptr(yo), _ptr(yf), _ptr(y0bar), _ptr(thbar), block, grid,
                     _stream_handle(stream), int(wide))
     sol.args.stream = v.stream
+    sol._in_use_on(stream)
     gs_solve_vjp(sol.args, v)
     return y0bar, thbar
 
@@ -530,6 +547,7 @@ def dense_eval(sol: Solution, t_query, stream=None):
     if tq.dim() != 2 or tq.shape[1] != p.n:
         raise ValueError("t_query must be [Q][n]")
     yq = torch.empty((p.d, tq.shape[0], p.n), dtype=torch.float64, device=p.y0.device)
+    sol._in_use_on(stream)
     gs_dense_eval(sol.args, tq.shape[0], tq.data_ptr(), yq.data_ptr(), _stream_handle(stream))
     return yq
 
