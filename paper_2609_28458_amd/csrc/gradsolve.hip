@@ -886,7 +886,6 @@ gs_status gs_de_profile(const gs_de_profile_args* A) {
   const int blk = 256;
   const int grd = (int)((n + blk - 1) / blk);
   const int grd3 = (int)((3 * n + blk - 1) / blk);
-  const unsigned grd_gn = (unsigned)((n * gs::de::kNodeLanes + blk - 1) / blk);
   hipStream_t s = static_cast<hipStream_t>(A->stream);
   hipLaunchKernelGGL(de_setup_kernel, dim3(grd3), dim3(blk), 0, s, n, D(L.scal), A->N_start,
                      A->rtol, A->atol, D(L.y0));
@@ -956,19 +955,26 @@ gs_status gs_de_profile(const gs_de_profile_args* A) {
   g.chi2_prev = A->chi2_prev;
   g.decrement = A->decrement;
   g.status_out = A->status;
+  auto gauss_newton = [&]() {
+    for (g.first = 0; g.first < n; g.first += gs::de::kFitsPerLaunch) {
+      const int64_t lanes = std::min(n - g.first, gs::de::kFitsPerLaunch) * gs::de::kNodeLanes;
+      hipLaunchKernelGGL(gs::de::gn_kernel, dim3((unsigned)((lanes + blk - 1) / blk)), dim3(blk), 0,
+                         s, g);
+    }
+  };
   for (int it = 0; it < A->iters; ++it) {
     shoot();
     sens_launches(&a, &both);
     g.update = 1;
     g.dist = nullptr;
-    hipLaunchKernelGGL(gs::de::gn_kernel, dim3(grd_gn), dim3(blk), 0, s, g);
+    gauss_newton();
   }
   // chi2 and distances at the returned parameters, the amplitude flat there
   shoot();
   sens_launches(&a, &both);
   g.update = 0;
   g.dist = A->dist;
-  hipLaunchKernelGGL(gs::de::gn_kernel, dim3(grd_gn), dim3(blk), 0, s, g);
+  gauss_newton();
   hipLaunchKernelGGL(gs::de::finish_kernel, dim3(grd), dim3(blk), 0, s, n, D(L.theta), A->a0,
                      A->omega_m);
   return hipGetLastError() == hipSuccess ? GS_OK : GS_ERR_HIP;

@@ -134,6 +134,7 @@ __global__ void spline_weights_kernel(int32_t K, const double* u, int32_t Kd, co
 // column 0 = d/da0 and column 1 = d/dOm.
 struct GnArgs {
   int64_t n;
+  int64_t first;          // the launch's first fit
   int32_t K;
   const double* N_nodes;  // [K]
   const double* y_out;    // [3][K][n]
@@ -163,6 +164,12 @@ struct GnArgs {
 // data points: 127 us with one lane each, now 35.
 constexpr int kNodeLanes = 8;
 
+// Fits per launch: a launch holds fewer than 2^32 lanes in all, which eight to a
+// fit reach at 2^29 fits (155 GB of arrays, so they fit the memory).  2^24 fits
+// run for about 50 ms, so a further launch costs nothing.
+constexpr int64_t kFitsPerLaunch = (int64_t)1 << 24;
+static_assert(kFitsPerLaunch * kNodeLanes < (int64_t)1 << 32, "lanes of a launch");
+
 // Sum over the lanes of a fit, in every lane of it.
 __device__ __forceinline__ double fit_sum(double v) {
 #pragma unroll
@@ -175,8 +182,8 @@ __global__ void __launch_bounds__(256) gn_kernel(GnArgs A) {
   const int64_t n = A.n;
   // All lanes of a wavefront take part in the sums; those past the last fit
   // repeat it and write nothing.
-  const bool mine = g / kNodeLanes < n;
-  const int64_t i = mine ? g / kNodeLanes : n - 1;
+  const bool mine = A.first + g / kNodeLanes < n;
+  const int64_t i = mine ? A.first + g / kNodeLanes : n - 1;
   const int l = (int)(threadIdx.x & (kNodeLanes - 1));
   const double a0 = A.theta[i], lam = A.theta[n + i], om = A.theta[2 * n + i];
   const double orad = A.theta[3 * n + i];
