@@ -176,18 +176,20 @@ typedef struct gs_solve_args {
   int32_t schedule;      /* gs_schedule                                     */
   int32_t block;         /* lanes per workgroup: 64, 128, 192 or 256        */
   int32_t grid;          /* workgroups of the persistent grid               */
-  int32_t refill;        /* refill a wavefront once this many lanes idle,
-                            1..64 (0: 8)                                    */
+  int32_t refill;        /* refill a wavefront of single (or tangent) lanes
+                            once this many lanes idle, 1..64 (0: 8); groups
+                            refill one by one                               */
   int32_t wide;          /* the first `wide` trajectories of the queue order
                             run on 16 lanes each (one state component per
                             lane) in the same launch, for the long tail of
                             uneven ensembles; results are bit-identical to
-                            one lane per trajectory.  0 = automatic: all of
-                            a small ensemble under the queue schedule (up to
-                            one wavefront of groups per SIMD; the static
-                            schedule never takes groups), the longest 512
-                            of orbits the library orders by itself, else
-                            none.  > 0
+                            one lane per trajectory.  0 = automatic, under
+                            the queue schedule only: all of a small ensemble
+                            (up to one wavefront of groups per SIMD) unless
+                            `grid` holds fewer than its groups at once; the
+                            longest 512 of taped orbits the library orders
+                            by itself unless `grid` holds less than a
+                            wavefront per SIMD; else none.  > 0
                             needs the queue schedule (else
                             GS_ERR_UNSUPPORTED); the tape (either mode) and
                             output nodes are written record for record as
@@ -351,9 +353,10 @@ gs_status gs_solve_vjp(const gs_solve_args* fwd, const gs_vjp_args* vjp);
  * S_final [d][M][n] and, when K > 0, S_out [d][M][K][n]: S[c][m] is
  * d y_c / d input_m; for shared theta (theta_stride 0) it is the derivative
  * of each trajectory with respect to the shared value.  All columns run in one
- * launch, one lane per tangent, for small ensembles and for the systems whose
- * tangents do not fit one lane's registers; otherwise two columns per launch
- * in one lane, `wide` putting the head of the order on one lane per tangent.
+ * launch, one lane per tangent, for small ensembles (on a caller's `grid`, if
+ * that holds their lanes) and for the systems whose tangents do not fit one
+ * lane's registers; otherwise two columns per launch in one lane, `wide` putting
+ * the head of the order on one lane per tangent.
  * Values and tangents are the same, bit for bit, either way.  No tape; queue
  * schedule only.  1 <= M <= 16. */
 typedef struct gs_sens_args {

@@ -361,14 +361,34 @@ int64_t* own_order(const gs_solve_args* a, bool refills) {
 // and a half wavefronts per CU on, workgroups of one wavefront are placed
 // unevenly over the SIMDs (65,536 orbits 1.52 against 1.06 ms).
 int auto_block(int64_t lanes) { return lanes <= (int64_t)96 * num_cus() ? 64 : 256; }
+// A grid given without a block counts workgroups of four wavefronts unless it
+// holds the lanes with one in each: smaller workgroups would hold fewer
+// trajectories than the caller made room for (4,096 orbits on 16 workgroups, adjoint
+// 0.94 ms with one wavefront in each, 0.52 with four; on 64: 0.41 and 0.52).
+int block_of(int32_t block, int32_t grid, int64_t lanes) {
+  if (block > 0) return block;
+  return grid > 0 && (int64_t)grid * 64 < lanes ? 256 : auto_block(lanes);
+}
+
+// Whether a caller's grid, if there is one, holds `lanes` lanes at once.  The
+// lines below at which a trajectory takes several lanes are drawn for a full chip:
+// a grid that holds 4,096 orbits one lane each would hold 256 on groups, sixteen
+// rounds at half the time an attempt (Dopri5 without outputs, 16 workgroups of
+// 256: 1.37 ms on groups, 0.39 on one lane each).
+int64_t held_by_grid(const gs_solve_args* a, int64_t lanes) {
+  return a->grid > 0 ? (int64_t)a->grid * block_of(a->block, a->grid, lanes) : INT64_MAX;
+}
+bool grid_holds(const gs_solve_args* a, int64_t lanes) { return held_by_grid(a, lanes) >= lanes; }
 
 // Trajectories at the head of the order on 16-lane groups: the caller's
 // `wide`, or all of a small ensemble, as many groups as one wavefront per
 // SIMD holds.  A group's attempt takes fewer instructions than a lane's
 // (1,000 orbits with 64 outputs 1.04 ms against 2.17 on one lane each, 4,096
 // binaries from r = 100 8.3 against 9.7, 4,096 quintessence models with 7
-// outputs 43 us against 52); with twice as many groups two wavefronts share a
-// SIMD (8,192 models 69 us against 53).
+// outputs 43 us against 52; Dopri5 without outputs, 4,096 oscillators 102 us
+// against 120, 4,096 Kepler orbits 306 against 345, one of them 163 against 181);
+// with twice as many groups two wavefronts share a SIMD (8,192 models 69 us
+// against 53).
 //
 // Behind the library's own order of taped orbits the longest 512 take groups:
 // the launch ends with its longest orbit (gradient of 20,000 orbits 8.1 -> 7.3
@@ -377,8 +397,11 @@ constexpr int64_t kOwnHead = 512;
 int64_t wide_of(const gs_solve_args* a) {
   if (a->wide > 0) return std::min<int64_t>(a->wide, a->n);
   if (a->schedule != GS_SCHED_QUEUE || is_stiff(a)) return 0;
-  if (a->n <= (int64_t)16 * num_cus()) return a->n;
-  return a->rhs == GS_RHS_LOGHALO && own_order(a, false) ? kOwnHead : 0;
+  if (a->n <= (int64_t)16 * num_cus() && grid_holds(a, a->n * gs::kGroup)) return a->n;
+  // The head's groups are an eighth of a full chip's lanes.
+  return a->rhs == GS_RHS_LOGHALO && own_order(a, false) && grid_holds(a, (int64_t)256 * num_cus())
+             ? kOwnHead
+             : 0;
 }
 
 // Grid of the forward launch: static mode covers n lanes; the persistent
@@ -388,7 +411,7 @@ int64_t wide_of(const gs_solve_args* a) {
 void solve_shape(const gs_solve_args* a, int64_t n_wide, int* grid, int* block, int64_t* limit,
                  bool defer) {
   const int64_t lanes = n_wide == a->n ? n_wide * gs::kGroup : a->n;
-  const int b = a->block > 0 ? a->block : is_stiff(a) ? 256 : auto_block(lanes);
+  const int b = is_stiff(a) && a->block == 0 ? 256 : block_of(a->block, a->grid, lanes);
   const int64_t need = (a->n + b - 1) / b;
   int64_t lim = need;
   if (a->schedule == GS_SCHED_STATIC) {
@@ -656,7 +679,11 @@ gs_status gs_solve_vjp(const gs_solve_args* fwd, const gs_vjp_args* v) {
   // Workgroups of one wavefront up to one per two SIMDs, as in auto_block (2,000
   // orbits 0.78 against 0.96 ms, 20,000 binaries 17.2 against 19.5 ms, 40,000
   // binaries 19.9 against 19.5 ms).
-  int block = v->block > 0 ? v->block : fwd->n <= (int64_t)128 * num_cus() ? 64 : 256;
+  int block = v->block;
+  if (block == 0) {
+    const bool held = v->grid == 0 || (int64_t)v->grid * 64 >= fwd->n;
+    block = held && fwd->n <= (int64_t)128 * num_cus() ? 64 : 256;
+  }
   while (block > 64 && lds_lane * block > max_lds_per_block()) block -= 64;
   if (lds_lane * block > max_lds_per_block()) return GS_ERR_UNSUPPORTED;
   hipStream_t s = static_cast<hipStream_t>(v->stream);
@@ -727,13 +754,18 @@ int64_t tangent_lanes_each(int M) {
 // us, 24,000 orbits 726 against 697, 32,000 orbits 737 against 700; 1 column:
 // 32,000 orbits 441 against 522 us, 64,000 744 against 509); against several
 // at one and a half for each (9 columns: 32,000 orbits 1.85 against 3.29 ms,
-// 64,000 orbits 3.25 against 3.22).
+// 64,000 orbits 3.25 against 3.22).  On a caller's grid that holds less than
+// the chip the lanes go round: 4,096 orbits on 16 workgroups, 2 columns 1.29 ms
+// in four rounds against 1.03, 9 columns 2.9 in twelve against five launches of
+// 4.8 in all.
 // Pairs without dual-number kernels always take tangent lanes.
 bool on_tangent_lanes(const gs_solve_args* a, int M, const Ops& o) {
   if (!o.sens_dual[a->K > 0 ? 1 : 0]) return true;
-  const int64_t launches = (M + 1) / 2;
-  const int64_t waves_per_cu = launches == 1 ? 4 : launches * 6;
-  return a->n * tangent_lanes_each(M) <= waves_per_cu * 64 * num_cus();
+  const int64_t launches = (M + 1) / 2, lanes = a->n * tangent_lanes_each(M);
+  const int64_t chip = (int64_t)256 * num_cus();
+  const int64_t held = std::min(chip, held_by_grid(a, lanes));
+  return launches == 1 ? lanes <= held
+                       : lanes <= launches * std::min(chip * 3 / 2, held * 7 / 2);
 }
 
 // The launches of a sensitivity solve whose arguments have been checked.
@@ -743,7 +775,7 @@ void sens_launches(const gs_solve_args* a, const gs_sens_args* sa) {
   const gs_host::Ops& o = ops(a->rhs, a->tableau);
   const bool tangent_lanes = on_tangent_lanes(a, sa->M, o);
   const int64_t lanes = tangent_lanes ? a->n * tangent_lanes_each(sa->M) : a->n;
-  const int block = a->block > 0 ? a->block : auto_block(lanes);
+  const int block = block_of(a->block, a->grid, lanes);
   gs::SensParams S;
   std::memset(&S, 0, sizeof S);
   S.m_total = sa->M;
