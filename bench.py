@@ -270,10 +270,11 @@ def headline_rows(args, torch, api, inputs, autotune, w, prob, sol, graph, cost,
 
     ms_kernel = timed(direct, 2, 0, torch)
     achieved = attempts * fpa / (ms_kernel * 1e-3) / 1e12
-    # Its critical path: the longest binary alone on one lane.
+    # Its critical path: the longest binary alone on one lane (under the queue
+    # schedule a single trajectory runs on a group by itself).
     i_long = int(torch.argmax(att_each))
     one = subset(w, [i_long])
-    lsol = api.Solution(mk(api, one), api.Launch(block=64))
+    lsol = api.Solution(mk(api, one), api.Launch(schedule="static", block=64))
     ms_lone = timed(lambda: lsol.run(), 1, 1, torch)
     traffic, traffic_src = committed_traffic()
     roofline = {
@@ -396,7 +397,7 @@ def c2_uneven(args, torch, api, inputs, autotune):
     achieved = attempts * fpa / (ms_kernel * 1e-3) / 1e12
     i_long = int(torch.argmax(att_each))
     lprob = mk(api, subset(w, [i_long]))
-    ms_lone = timed(lambda: api.solve(lprob, api.Launch(block=64)), 3, 1, torch)
+    ms_lone = timed(lambda: api.solve(lprob, api.Launch(schedule="static", block=64)), 3, 1, torch)
     ms_group = timed(lambda: api.solve(lprob, api.Launch(block=64, wide=1)), 3, 1, torch)
     # accuracy: final states of 10,000 orbits against Verner 7 at 1e-13
     idx = np.sort(np.random.default_rng(18).choice(n, 10_000, replace=False))
@@ -599,7 +600,8 @@ def c3_gradient(torch, api, inputs, autotune):
     ach_vjp = steps_g * fvs / (ms_vjp * 1e-3) / 1e12
     i_g = int(torch.argmax(fused.n_accepted))
     p1 = mk(api, subset(wg, [i_g]))
-    s1 = api.Solution(p1, api.Launch(block=64, ckpt_every=1, ckpt_capacity=cap1))
+    s1 = api.Solution(p1, api.Launch(schedule="static", block=64, ckpt_every=1,
+                                     ckpt_capacity=cap1))
     ms_f1 = timed(lambda: s1.run(), 3, 1, torch)
     yb1 = torch.ones((1, 6, 1), dtype=torch.float64, device="cuda")
     ms_v1 = timed(lambda: api.solve_vjp(s1, ybar_final=yb1), 3, 1, torch)
@@ -621,13 +623,13 @@ def c3_gradient(torch, api, inputs, autotune):
         f"longest orbit's adjoint alone {ms_v1:.3f} ms ({ms_v1g:.3f} ms on a group); "
         f"alone by launch {adj_alone}")
     del fused, s1
-    # forward sensitivities (the paper's own derivative), 2 and 9 columns, one
-    # lane per orbit or the longest 256 on 16-lane groups (the batch is bound
-    # by its longest orbit), reported at the faster
+    # forward sensitivities (the paper's own derivative), 2 and 9 columns, dual
+    # numbers in one lane per orbit, or the longest 256 on one lane per tangent
+    # (the batch is bound by its longest orbit), reported at the faster
     sens = {}
     for cols in ([6, 7], list(range(9))):
         by = {}
-        for lname, L in (("lanes", api.Launch()), ("256 on groups", api.Launch(wide=256))):
+        for lname, L in (("lanes", api.Launch()), ("256 on tangent lanes", api.Launch(wide=256))):
             by[lname] = round(timed(lambda: api.solve_sens(pg, cols, L, order=gorder), reps, 1,
                                     torch), 4)
         fast = min(by, key=by.get)
@@ -897,11 +899,9 @@ def precession_gradient(torch, api, inputs):
     ms_st = timed(tilt_grads, 1, 1, torch)
     tape_gb = sol.workspace.numel() / 1e9
     del sol
-    sens_by = {}
-    for name, L, o in (("lanes", api.Launch(), None),
-                       ("all on groups", api.Launch(wide=n), order)):
-        sens_by[name] = round(timed(lambda: api.solve_sens(prob, [9, 10, 11], L, order=o), 1, 1,
-                                    torch), 2)
+    # three columns, all on tangent lanes (their dual numbers do not fit one lane)
+    sens_by = {"tangent lanes, longest first": round(timed(
+        lambda: api.solve_sens(prob, [9, 10, 11], order=order), 1, 1, torch), 2)}
     ms_s = min(sens_by.values())
     res = {"workload": f"{n} binaries, r = 1000 -> 10, Verner 7 3.16e-9, losses: both final "
                        "tilt angles, parameters (q, chi1, chi2)",
@@ -1006,7 +1006,8 @@ def main():
         graph.launch()
         torch.cuda.synchronize()
         i_long = int(torch.argmax(sol.n_accepted + sol.n_rejected))
-        lsol = api.Solution(mk(api, subset(w, [i_long])), api.Launch(block=64))
+        lsol = api.Solution(mk(api, subset(w, [i_long])),
+                            api.Launch(schedule="static", block=64))
         lsol.run()
         torch.cuda.synchronize()
         print(json.dumps({"attempts": int((lsol.n_accepted + lsol.n_rejected).item())}))
