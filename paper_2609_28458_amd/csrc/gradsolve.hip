@@ -508,16 +508,27 @@ const int64_t* queue_order_of(const gs_solve_args* a, bool refills, hipStream_t 
 }
 
 // Most outputs per trajectory that a small launch of groups evaluates in the
-// loop (a pair with a dense polynomial).  An output then holds its wavefront
-// for about 0.1 us; deferred outputs cost one launch more, about 5 us
-// (quintessence, 16 models with 7 outputs 42.6 us, 40.6 in the loop; 500 models
-// with 8 outputs 44.3 and 42.5, with 64 outputs 71 and 92).  The values are the same bit for bit.
-constexpr int kInLoopNodes = 8;
+// loop (a pair with a dense polynomial).  An output then holds its wavefront;
+// deferred outputs cost one launch more, about 5 us.  The values are the same bit
+// for bit.  The line is where both take the same time, which depends on the system
+// (Dopri5, deferred / in the loop, 16 models: quintessence 8 outputs 41.9 / 40.5 us,
+// 12 outputs 43.1 / 43.0; Kepler 60.9 / 60.9, 64.0 / 66.7; log halo 4 outputs
+// 47.2 / 46.9, 8 outputs 51.0 / 52.4; oscillator 34.1 / 34.4, 37.6 / 39.2; at 500
+// and 4,096 models the same within an output or two).  The binaries' kernel with
+// outputs in its loop is the slower one from the first output on (114 / 120 us).
+int in_loop_nodes(int rhs) {
+  switch (rhs) {
+    case GS_RHS_QUINT:
+    case GS_RHS_KEPLER: return 8;
+    case GS_RHS_SPINPREC: return 0;
+    default: return 4;
+  }
+}
 
 gs_status launch_solve_all(const gs_solve_args* a, bool defer = true) {
   hipStream_t s = static_cast<hipStream_t>(a->stream);
   const int64_t n_wide = wide_of(a);
-  if (n_wide == a->n && a->K <= kInLoopNodes && a->ckpt_every == 0) defer = false;
+  if (n_wide == a->n && a->K <= in_loop_nodes(a->rhs) && a->ckpt_every == 0) defer = false;
   Params P = make_params(a, defer);
   P.n_wide = n_wide;
   int grid = 0, block = 0;
