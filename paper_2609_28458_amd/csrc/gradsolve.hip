@@ -126,7 +126,7 @@ OrderLayout order_layout(int64_t n) {
 
 // The library orders an ensemble by itself, longest first, where the caller
 // gives no order, the built-in model ranks the costs well, and the solve is
-// long against the order's cost, which has to show without reading device
+// long against the order's 0.1 ms, which has to show without reading device
 // memory:
 //  - precessing binaries (any span: their steps cost microseconds and their
 //    costs differ several times) once the launch cannot hold them all, from
@@ -139,10 +139,13 @@ OrderLayout order_layout(int64_t n) {
 //    together (gradient of 100,000 orbits to t = 100: forward with tape and
 //    adjoint 16.1 ms in index order, 10.4 ms).
 // Other orbits take 0.1 to 16 ms and are left to gs_queue_order.
-// The order itself takes 24 us for 16,384 orbits, 59 for 262,144, 161 for 10^6.
-// Orbits that end after 35 steps, in a tape with room for 256, gain or lose up to
-// 6% by it (65,536 of them, forward and adjoint 205 us without, 216 with it); ones
-// that end after five pay for it (75 and 116 us), which the host cannot see.
+// The order takes 45 us for 16,384 orbits, 150 for 262,144, 510 for 10^6, and a
+// solve that ends after a few steps in a tape with room for 256 pays for it, which the host
+// cannot see (65,536 orbits, forward and adjoint: 35 steps 205 us without, 249 with
+// it; 290 steps 924 and 819).  Faster key and prefix-sum kernels (16,384 orbits in 24
+// us) made the long solves slower: the solve then starts on a queue that has
+// run dry, its wavefronts reach the work queue out of order, and the longest
+// orbits share SIMDs (gradient of 100,000 orbits 10.2 -> 11.7 ms).
 constexpr int64_t kAutoOrderMin = 16384;
 bool orders_tape(const gs_solve_args* a) {
   return (a->rhs == GS_RHS_LOGHALO || a->rhs == GS_RHS_SPINPREC) && a->n >= kAutoOrderMin &&
@@ -491,8 +494,7 @@ void launch_order(const gs_solve_args* a, const double* cost, int64_t* order, ch
   const int grid = (int)((a->n + 255) / 256);
   hipLaunchKernelGGL(gs::order::clear_kernel, dim3(gs::order::kBuckets / 256), dim3(256), 0, s,
                      w);
-  hipLaunchKernelGGL(gs::order::key_kernel, dim3(std::min(grid, gs::order::kKeyBlocks)), dim3(256),
-                     0, s, c, w);
+  hipLaunchKernelGGL(gs::order::key_kernel, dim3(grid), dim3(256), 0, s, c, w);
   hipLaunchKernelGGL(gs::order::bucket_kernel, dim3(grid), dim3(256), 0, s, a->n, w);
   hipLaunchKernelGGL(gs::order::scan_kernel, dim3(1), dim3(gs::order::kScanThreads), 0, s, w);
   hipLaunchKernelGGL(gs::order::scatter_kernel, dim3(grid), dim3(256), 0, s, a->n, w, order);

@@ -8,7 +8,7 @@
 // buckets of the key range puts the largest keys first:
 //   1. clear the histogram and the key range,
 //   2. key of every trajectory, and the range of the finite keys (one
-//      64-bit atomic min/max per workgroup on order-preserving integer
+//      64-bit atomic min/max per wavefront on order-preserving integer
 //      images of the keys),
 //   3. bucket of every key (descending; non-finite keys in the last bucket)
 //      and the bucket histogram,
@@ -109,39 +109,25 @@ __device__ __forceinline__ double cost_key(const CostIn& c, int64_t i) {
   return lk;
 }
 
-// Keys and their range.  A workgroup takes its keys in turn and puts one pair
-// of atomics on the range: one pair per wavefront made the kernel wait for them, 16,384
-// on one address (10^6 orbits 360 us, now 30; 262,144: 97, now 18).
-constexpr int kKeyBlocks = 512;
 __global__ void __launch_bounds__(256) key_kernel(CostIn c, Ws w) {
-  __shared__ unsigned long long part[2][4];
-  unsigned long long lo = ~0ull, hi = 0ull;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < c.n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const double k = cost_key(c, i);
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  double k = 0.0;
+  bool fin = false;
+  if (i < c.n) {
+    k = cost_key(c, i);
     w.key[i] = k;
-    if ((k - k) == 0.0) {
-      const unsigned long long b = ord_bits(k);
-      lo = b < lo ? b : lo;
-      hi = b > hi ? b : hi;
-    }
+    fin = (k - k) == 0.0;
   }
-  auto merge = [&](unsigned long long olo, unsigned long long ohi) {
+  unsigned long long lo = fin ? ord_bits(k) : ~0ull;
+  unsigned long long hi = fin ? ord_bits(k) : 0ull;
+  // wavefront min / max, then one atomic per wavefront
+  for (int off = 32; off > 0; off >>= 1) {
+    const unsigned long long olo = __shfl_xor(lo, off);
+    const unsigned long long ohi = __shfl_xor(hi, off);
     lo = olo < lo ? olo : lo;
     hi = ohi > hi ? ohi : hi;
-  };
-  for (int off = 32; off > 0; off >>= 1) {
-    const unsigned long long olo = __shfl_xor(lo, off), ohi = __shfl_xor(hi, off);
-    merge(olo, ohi);
   }
-  if ((threadIdx.x & 63) == 0) {
-    part[0][threadIdx.x >> 6] = lo;
-    part[1][threadIdx.x >> 6] = hi;
-  }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  for (int v = 1; v < 4; ++v) merge(part[0][v], part[1][v]);
-  if (lo != ~0ull) {
+  if ((threadIdx.x & 63) == 0 && lo != ~0ull) {
     atomicMin(w.range, lo);
     atomicMax(w.range + 1, hi);
   }
@@ -162,38 +148,29 @@ __global__ void __launch_bounds__(256) bucket_kernel(int64_t n, Ws w) {
   atomicAdd(w.hist + b, 1u);
 }
 
-// Exclusive prefix sum of the histogram in place, in one workgroup.  Each
-// wavefront holds its 4,096 counts in registers, read and written in whole lines
-// (each thread walking 64 counts of its own twice took 27 us, now 9).
+// Exclusive prefix sum of the histogram in place, one workgroup of
+// kScanThreads threads, each owning kBuckets / kScanThreads buckets.
 __global__ void __launch_bounds__(kScanThreads) scan_kernel(Ws w) {
-  constexpr int kWaves = kScanThreads / 64, kRows = kBuckets / (kScanThreads * 4);
-  static_assert(kRows * kScanThreads * 4 == kBuckets, "whole rows of four counts a lane");
-  __shared__ uint32_t part[kWaves];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint4* h = reinterpret_cast<uint4*>(w.hist) + wave * kRows * 64 + lane;
-  uint4 v[kRows];
-  uint32_t total = 0;
-#pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-    v[r] = h[r * 64];
-    total += v[r].x + v[r].y + v[r].z + v[r].w;
-  }
-  for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off);
-  if (lane == 0) part[wave] = total;
+  constexpr int per = kBuckets / kScanThreads;
+  __shared__ uint32_t part[kScanThreads];
+  const int t = threadIdx.x;
+  uint32_t* h = w.hist + t * per;
+  uint32_t sum = 0;
+  for (int j = 0; j < per; ++j) sum += h[j];
+  part[t] = sum;
   __syncthreads();
-  uint32_t run = 0;  // of all counts before the row
-  for (int u = 0; u < wave; ++u) run += part[u];
-#pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-    const uint32_t own = v[r].x + v[r].y + v[r].z + v[r].w;
-    uint32_t incl = own;  // of the lanes up to this one
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t o = __shfl_up(incl, off);
-      incl += lane >= off ? o : 0u;
-    }
-    const uint32_t at = run + incl - own;
-    h[r * 64] = make_uint4(at, at + v[r].x, at + v[r].x + v[r].y, at + v[r].x + v[r].y + v[r].z);
-    run += __shfl(incl, 63);
+  // Hillis-Steele inclusive scan of the per-thread sums
+  for (int off = 1; off < kScanThreads; off <<= 1) {
+    const uint32_t v = t >= off ? part[t - off] : 0u;
+    __syncthreads();
+    part[t] += v;
+    __syncthreads();
+  }
+  uint32_t run = part[t] - sum;  // exclusive
+  for (int j = 0; j < per; ++j) {
+    const uint32_t c = h[j];
+    h[j] = run;
+    run += c;
   }
 }
 
