@@ -203,11 +203,19 @@ typedef struct gs_solve_args {
                             workgroup.                                      */
   const int64_t* order;  /* [n] queue order (a permutation of 0..n-1), or
                             NULL: 0, 1, ..., n-1, or the library's own
-                            longest-first order for 16,384 or more binaries
-                            and for as many orbits or binaries with a tape
-                            of 256 steps or more (results do not depend on
-                            the order); gs_solve_vjp takes the
-                            trajectories in the same order.  Device memory,
+                            longest-first order.  Under the queue schedule,
+                            given room for it in the workspace, it builds
+                            one for 16,384 or more
+                             - orbits or binaries with a tape of 256 steps
+                               or more (the adjoint takes the same order);
+                             - binaries without one that are more than the
+                               launch holds, if `wide` is 0 (else the head
+                               is the first `wide` by index), and their
+                               sensitivities on tangent lanes.
+                            Results do not depend on the order.
+                            gs_solve_vjp takes the trajectories in the
+                            caller's order, or in the library's where the
+                            forward built it for a tape.  Device memory,
                             read on the device only: entries outside [0, n)
                             are skipped, and before the solve every status
                             is set to GS_TRAJ_NOT_RUN, so an index the order
